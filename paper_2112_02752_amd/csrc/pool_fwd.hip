@@ -2,14 +2,31 @@
 //
 //   out[m][d] = scale_m * sum_{j in bag m} W[row_offset[t(m)] + idx[j]][d]
 //
-// One wavefront per bag.  A row of D*sizeof(T) bytes is read as 16-byte
-// vectors by a group of G lanes (G a power of two), so one wave instruction
-// gathers 64/G rows; each group walks its share of the bag with UNROLL rows
-// in flight, accumulating in fp32.  The groups are summed with a butterfly at
-// the end and group 0 stores the pooled row.  Ids of the bag are read 64 at a
-// time with one coalesced load; repeated ids of such a chunk are merged (one
-// row load, added with its multiplicity) and the distinct ids are handed to
-// the groups by lane shuffles.
+// A row of D*sizeof(T) bytes is read as 16-byte vectors by a group of G lanes
+// (G a power of two), so one wave instruction gathers R = 64/G rows.  A
+// wavefront sums one bag: its ids are read 64 at a time, lane g*G + u taking
+// id u*R + g, so that the ids of lane group g already sit in that group's own
+// lanes and reach all of them by a lane broadcast within the group (DPP for
+// groups of up to 16 lanes), with no trip through LDS.  Up to 8 rows per lane
+// group are in flight; the groups are summed across the wavefront at the end
+// (gfx950 row and half swaps).  Repeated ids of a bag are loaded again: a hot
+// row is a cache hit, and finding the repeats cost more instructions than
+// their loads.
+//
+// What bounds it: the rows the L2s miss, once the instructions per row are few
+// enough.  Merging repeats by hash classes, LDS shuffles and a select per
+// element, the kernel issued 640 vector instructions per bag of the 26-table
+// bf16 workload (136M per call, about the kernel's whole 200 us on 1024 SIMDs
+// at 4 cycles each); it issues 45M now and takes 135 us at 5.0 TB/s of L2 miss
+// traffic (571 MB read, 109 MB written), the rate of a large device copy.  One
+// 50M-row table, 16384 bags of 30 ids: 14-15 us either way (latency of four
+// dependent loads); 8 tables of 1M rows: 22 -> 18.5 us (4.8 TB/s).
+//
+// Short bags: a wavefront per bag of one id leaves 63/64 of its loads unused
+// and takes as long as a full one, so when the bags of a wavefront and its
+// neighbours (four in all, or as many as there are lane groups) hold at most
+// kShortBag ids each (one round of loads per lane group), the first of these
+// wavefronts sums one bag per lane group and the others leave at once.
 #include "emb_common.h"
 #include "kernels.h"
 
@@ -18,145 +35,280 @@ namespace emb {
 namespace {
 
 template <typename TW>
-struct Vec;  // 16 bytes of table row, widened to fp32
+struct Vec;  // 16 bytes of table row, added to fp32 accumulators
 
 // (loaded raw, widened where it is used, so that every load of a round is
 // issued before the first one is waited for)
 template <>
 struct Vec<float> {
   static constexpr int kElems = 4;
-  __device__ __forceinline__ static uint4 load(const float* p) { return *reinterpret_cast<const uint4*>(p); }
-  __device__ __forceinline__ static void widen(const uint4& v, float (&o)[4]) {
-    o[0] = __uint_as_float(v.x);
-    o[1] = __uint_as_float(v.y);
-    o[2] = __uint_as_float(v.z);
-    o[3] = __uint_as_float(v.w);
+  __device__ __forceinline__ static void add(const uint4& v, float (&o)[4]) {
+    o[0] += __uint_as_float(v.x);
+    o[1] += __uint_as_float(v.y);
+    o[2] += __uint_as_float(v.z);
+    o[3] += __uint_as_float(v.w);
   }
 };
 
 template <>
 struct Vec<uint16_t> {
   static constexpr int kElems = 8;
-  __device__ __forceinline__ static uint4 load(const uint16_t* p) { return *reinterpret_cast<const uint4*>(p); }
-  __device__ __forceinline__ static void widen(const uint4& v, float (&o)[8]) {
+  __device__ __forceinline__ static void add(const uint4& v, float (&o)[8]) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      o[2 * i] = __uint_as_float(w[i] << 16);
-      o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+      o[2 * i] += __uint_as_float(w[i] << 16);
+      o[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
     }
   }
 };
 
-constexpr int unroll_for(int rpi) { return rpi == 1 ? 8 : (rpi == 2 ? 8 : (rpi == 4 ? 8 : 4)); }
-
-template <typename TW, int G, int NV, typename TI>
-__global__ __launch_bounds__(256) void k_pool_fwd(const TW* __restrict__ W, const int32_t* __restrict__ offsets,
-                                                  const TI* __restrict__ idx, TableOffsets ro, int32_t B,
-                                                  int32_t M, int32_t D, int32_t pool, float* __restrict__ out) {
-  constexpr int RPI = kWave / G;
-  constexpr int E = Vec<TW>::kElems;
-  constexpr int UN = unroll_for(RPI) / NV > 0 ? unroll_for(RPI) / NV : 1;  // rows in flight per lane group
-  const int lane = threadIdx.x & (kWave - 1);
-  // the bag is uniform across the wavefront: keep its bookkeeping scalar
-  const int m = __builtin_amdgcn_readfirstlane(blockIdx.x * (256 / kWave) + (threadIdx.x >> 6));
-  if (m >= M) return;
-  const int g = lane / G, sub = lane % G;
-  const uint32_t base = ro.off[m / B];
-  const int start = offsets[m], end = offsets[m + 1];
-
-  float acc[NV][E];
-#pragma unroll
-  for (int v = 0; v < NV; ++v)
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[v][e] = 0.f;
-
-  for (int j0 = start; j0 < end; j0 += kWave) {
-    const int n = min(kWave, end - j0);
-    const bool valid = lane < n;
-    const int my_id = valid ? (int)idx[j0 + lane] : 0;
-    // Skewed ids repeat within a bag: each distinct id of the chunk is loaded
-    // once and added with its multiplicity.  Lanes are classed by an 8-bit
-    // hash of the id (one ballot per hash bit); a lane whose id equals the
-    // lowest lane of its class is a duplicate of it, every other lane (the
-    // lowest lane itself, or a hash collision) loads its own row.
-    const uint32_t h = ((uint32_t)my_id * 0x9E3779B1u) >> 24;
-    uint64_t cls = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (h >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      cls &= bit ? bb : ~bb;
-    }
-    const int lead = valid ? (int)__builtin_ctzll(cls) : lane;
-    // (the shuffle runs on every lane: a lane switched off does not supply its value)
-    const int lead_id = __shfl(my_id, lead, kWave);
-    const bool dup = valid && lead != lane && lead_id == my_id;
-    const uint64_t dups = __ballot(dup);
-    const bool loader = valid && !dup;
-    const uint64_t lm = __ballot(loader);
-    const int nu = (int)__popcll(lm);
-    // compact the loaders' (id, multiplicity) into lanes 0..nu-1
-    const int dst = loader ? (int)lanes_below(lm) : nu + (int)lanes_below(~lm);
-    const int mult = loader ? 1 + (int)__popcll(dups & cls) * (lead == lane) : 0;
-    const int c_id = __builtin_amdgcn_ds_permute(dst * 4, my_id);
-    const int c_mult = __builtin_amdgcn_ds_permute(dst * 4, mult);
-    for (int i0 = 0; i0 < nu; i0 += RPI * UN) {
-      // every row load of the round is issued before the first is used (the
-      // raw 16 bytes are widened afterwards); unused slots load nothing and
-      // are dropped by a select below
-      uint4 raw[UN][NV];
-      float wt[UN];  // multiplicity; 0 marks an unused slot
-#pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int s = i0 + u * RPI + g;
-        const int id = __shfl(c_id, s & (kWave - 1), kWave);
-        const int mu = __shfl(c_mult, s & (kWave - 1), kWave);
-        wt[u] = s < nu ? (float)mu : 0.f;
-        const TW* rp = W + (size_t)(base + (uint32_t)id) * (size_t)D;
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const int c0 = (v * G + sub) * E;
-          raw[u][v] = make_uint4(0u, 0u, 0u, 0u);
-          if (s < nu && c0 < D) raw[u][v] = Vec<TW>::load(rp + c0);
-        }
-      }
-      // a row of multiplicity 1 is added exactly as a plain sum would add it
-#pragma unroll
-      for (int u = 0; u < UN; ++u)
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-          const bool use = wt[u] != 0.f && (v * G + sub) * E < D;
-          float x[E];
-          Vec<TW>::widen(raw[u][v], x);
-#pragma unroll
-          for (int e = 0; e < E; ++e) acc[v][e] = use ? __builtin_fmaf(wt[u], x[e], acc[v][e]) : acc[v][e];
-        }
-    }
+// value of lane (this lane's group)*G + u in every lane of the group
+template <int G>
+__device__ __forceinline__ uint32_t group_bcast(uint32_t v, int u, int g) {
+  if constexpr (G == 64) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, u);
+  } else {
+    static_assert(G == 32, "narrower groups use DPP");
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, u);
+    const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)v, u + 32);
+    return g ? b : a;
   }
+}
+template <int G, int U>
+__device__ __forceinline__ uint32_t group_bcast_dpp(uint32_t v) {
+  static_assert(U < G, "lane of the group");
+  const int x = (int)v;
+  if constexpr (G == 16) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp(x, 0x150 + U, 0xf, 0xf, true);  // row_newbcast:U
+  } else if constexpr (G == 8) {
+    // lanes 0-7 of a row (banks 0 and 1) from lane U, lanes 8-15 from lane 8 + U
+    const int lo = __builtin_amdgcn_mov_dpp(x, 0x150 + U, 0xf, 0xf, true);
+    return (uint32_t)__builtin_amdgcn_update_dpp(lo, x, 0x150 + 8 + U, 0xf, 0xc, false);
+  } else if constexpr (G == 4) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp(x, U * 0x55, 0xf, 0xf, true);  // quad_perm:[U,U,U,U]
+  } else if constexpr (G == 2) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp(x, U == 0 ? 0xa0 : 0xf5, 0xf, 0xf, true);  // [U,U,2+U,2+U]
+  } else {
+    return v;
+  }
+}
 
-  // sum the RPI groups (butterfly over the group index bits)
-#pragma unroll
-  for (int o = G; o < kWave; o <<= 1)
+// x summed over lanes l and l ^ O (O = 32 or 16: the gfx950 half and row swaps)
+template <int O>
+__device__ __forceinline__ float add_across(float x) {
+  if constexpr (O == 32) {
+    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  } else if constexpr (O == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  } else {
+    return x + __shfl_xor(x, O, kWave);
+  }
+}
+template <int O, int NV, int E>
+__device__ __forceinline__ void sum_groups(float (&acc)[NV][E]) {
+  if constexpr (O < kWave) {
 #pragma unroll
     for (int v = 0; v < NV; ++v)
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc[v][e] += __shfl_xor(acc[v][e], o, kWave);
+      for (int e = 0; e < E; ++e) acc[v][e] = add_across<O>(acc[v][e]);
+    sum_groups<O * 2>(acc);
+  }
+}
 
+// rows a lane group has in flight (for rows of NV vectors per lane)
+constexpr int slots_in_flight(int g, int nv) { return 8 / nv < 1 ? 1 : (8 / nv < g ? 8 / nv : g); }
+// bags short enough to be packed one per lane group
+constexpr int kShortBag = 8;
+
+struct FwdArgs {
+  const void* W;
+  const int32_t* offsets;
+  const void* idx;
+  int32_t B, M, D, pool;
+  uint32_t b_magic;  // floor(2^32 / B) (B > 1)
+  float* out;
+  TableOffsets ro;
+};
+
+// Slots [u0, u0 + UN) of every lane group (U0 the same number where it is a
+// constant).  `row` holds, in lane g*G + u, the table row of group g's slot u;
+// cnt is the group's number of slots.  Straight code: every load of the round
+// is issued before the first is waited for.  Not FULL: slots the group lacks
+// are read as zeros under a mask.
+template <typename TW, int G, int NV, int UN, bool FULL, int U0, int U = 0>
+__device__ __forceinline__ void load_slots(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
+                                           int cnt, int g, uint4 (&raw)[UN][NV]) {
+  if constexpr (U < UN) {
+    uint32_t r;
+    if constexpr (G >= 32) r = group_bcast<G>(row, u0 + U, g);
+    else r = group_bcast_dpp<G, U0 + U>(row);
+    const uint64_t off = (uint64_t)r * (uint64_t)rowbytes;
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+      if constexpr (FULL) {
+        raw[U][v] = *reinterpret_cast<const uint4*>(col[v] + off);
+      } else {
+        raw[U][v] = make_uint4(0u, 0u, 0u, 0u);
+        if (u0 + U < cnt) raw[U][v] = *reinterpret_cast<const uint4*>(col[v] + off);
+      }
+    }
+    load_slots<TW, G, NV, UN, FULL, U0, U + 1>(col, rowbytes, row, u0, cnt, g, raw);
+  }
+}
+template <typename TW, int G, int NV, int UN, bool FULL, int U0>
+__device__ __forceinline__ void add_slots(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
+                                          int cnt, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+  uint4 raw[UN][NV];
+  load_slots<TW, G, NV, UN, FULL, U0>(col, rowbytes, row, u0, cnt, g, raw);
+#pragma unroll
+  for (int u = 0; u < UN; ++u)
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Vec<TW>::add(raw[u][v], acc[v]);
+}
+
+// The slots of a chunk of ids from u0 on, nall of them present in every group
+// and nmax in some group (both uniform): whole rounds without masks, then one
+// masked round just long enough for what is left (a short bag does not pay
+// for a long round).
+template <typename TW, int G, int NV, int UN, int U0>
+__device__ __forceinline__ void add_rest(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
+                                         int cnt, int nmax, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+  if constexpr (UN > 1) {
+    if (nmax - u0 <= UN / 2) {
+      add_rest<TW, G, NV, UN / 2, U0>(col, rowbytes, row, u0, cnt, nmax, g, acc);
+      return;
+    }
+  }
+  add_slots<TW, G, NV, UN, false, U0>(col, rowbytes, row, u0, cnt, g, acc);
+}
+template <typename TW, int G, int NV, int U0 = 0>
+__device__ __forceinline__ void add_chunk(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int cnt,
+                                          int nall, int nmax, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+  constexpr int UN = slots_in_flight(G, NV);
+  if constexpr (G >= 32) {
+    int u0 = 0;
+    for (; u0 + UN <= nall; u0 += UN) add_slots<TW, G, NV, UN, true, 0>(col, rowbytes, row, u0, cnt, g, acc);
+    for (; u0 < nmax; u0 += UN) add_rest<TW, G, NV, UN, 0>(col, rowbytes, row, u0, cnt, nmax, g, acc);
+  } else if constexpr (U0 < G) {
+    if (U0 + UN <= nall) add_slots<TW, G, NV, UN, true, U0>(col, rowbytes, row, U0, cnt, g, acc);
+    else if (U0 < nmax) add_rest<TW, G, NV, UN, U0>(col, rowbytes, row, U0, cnt, nmax, g, acc);
+    if (U0 + UN < nmax) add_chunk<TW, G, NV, U0 + UN>(col, rowbytes, row, cnt, nall, nmax, g, acc);
+  }
+}
+
+template <typename TW, int G, int NV, typename TI>
+__global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
+  constexpr int R = kWave / G;
+  constexpr int E = Vec<TW>::kElems;
+  constexpr int P = R < 4 ? R : 4;  // bags a wavefront packs
+  const int lane = threadIdx.x & (kWave - 1);
+  // the bag is uniform across the wavefront: keep its bookkeeping scalar
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int m = (int)blockIdx.x * 4 + w;
+  if (m >= a.M) return;
+  const int g = lane / G, sub = lane % G;
+  const TI* idx = static_cast<const TI*>(a.idx);
+  const uint32_t rowbytes = (uint32_t)a.D * (uint32_t)sizeof(TW);
+
+  float acc[NV][E];
+  const char* col[NV];  // this lane's columns (lanes past the row's end stand in at column 0, stored by none)
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    const int c0 = (v * G + sub) * E;
+    col[v] = static_cast<const char*>(a.W) + (size_t)(c0 < a.D ? c0 : 0) * sizeof(TW);
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[v][e] = 0.f;
+  }
+
+  // table of a bag: the division by B as a multiplication, one too few at most
+  auto table_of = [&](int bag) {
+    uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag, a.b_magic) : (uint32_t)bag;
+    if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag) ++t;
+    return (int)t;
+  };
+
+  int first, last;  // the bag's ids
+  // the P bags of this wavefront and its neighbours, when they are all there
+  const int m0 = m - w % P;
+  if (P > 1 && a.B >= P && m0 + P <= a.M) {
+    int o[P + 1];
+#pragma unroll
+    for (int i = 0; i <= P; ++i) o[i] = a.offsets[m0 + i];
+    if constexpr (P > 1) {
+      int lmax = 0, lmin = kShortBag;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        lmax = max(lmax, o[i + 1] - o[i]);
+        lmin = min(lmin, o[i + 1] - o[i]);
+      }
+      if (lmax <= (kShortBag < G ? kShortBag : G)) {
+        if (w % P) return;
+        // one bag per lane group (groups past P have none)
+        int start = o[0], len = o[1] - o[0];
+#pragma unroll
+        for (int i = 1; i < P; ++i) {
+          start = g == i ? o[i] : start;
+          len = g == i ? o[i + 1] - o[i] : len;
+        }
+        if (g >= P) len = 0;
+        const int t = table_of(m0);
+        // P bags lie in at most two tables
+        const uint32_t base = m0 + g < (t + 1) * a.B ? a.ro.off[t] : a.ro.off[t + 1];
+        const uint32_t row = sub < len ? base + (uint32_t)(int32_t)idx[start + sub] : 0u;
+        add_chunk<TW, G, NV>(col, rowbytes, row, len, R > P ? 0 : lmin, lmax, g, acc);
+        const float scale = (a.pool == EMB_POOL_MEAN && len > 0) ? 1.0f / (float)len : 1.0f;
+        float* op = a.out + (size_t)(m0 + g) * (size_t)a.D;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          const int c0 = (v * G + sub) * E;
+          if (g < P && c0 < a.D) {
+#pragma unroll
+            for (int e = 0; e < E; e += 4)
+              *reinterpret_cast<float4*>(op + c0 + e) = make_float4(acc[v][e] * scale, acc[v][e + 1] * scale,
+                                                                    acc[v][e + 2] * scale, acc[v][e + 3] * scale);
+          }
+        }
+        return;
+      }
+    }
+    first = o[0];
+    last = o[1];
+#pragma unroll
+    for (int i = 1; i < P; ++i) {
+      first = w % P == i ? o[i] : first;
+      last = w % P == i ? o[i + 1] : last;
+    }
+  } else {
+    first = a.offsets[m];
+    last = a.offsets[m + 1];
+  }
+
+  // one bag: group g takes ids g, g + R, g + 2R, ... of every 64
+  const int start = __builtin_amdgcn_readfirstlane(first), end = __builtin_amdgcn_readfirstlane(last);
+  const uint32_t base = a.ro.off[table_of(m)];
+  for (int j0 = start; j0 < end; j0 += kWave) {
+    const int n = min(kWave, end - j0);
+    const int k = sub * R + g;
+    const uint32_t row = k < n ? base + (uint32_t)(int32_t)idx[j0 + k] : 0u;
+    add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, acc);
+  }
+  sum_groups<G>(acc);
+
+  const int L = end - start;
+  const float scale = (a.pool == EMB_POOL_MEAN && L > 0) ? 1.0f / (float)L : 1.0f;
+  float* op = a.out + (size_t)m * (size_t)a.D;
   if (g == 0) {
-    const int L = end - start;
-    const float scale = (pool == EMB_POOL_MEAN && L > 0) ? 1.0f / (float)L : 1.0f;
-    float* op = out + (size_t)m * (size_t)D;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       const int c0 = (v * G + sub) * E;
-      if (c0 < D) {
+      if (c0 < a.D) {
 #pragma unroll
-        for (int e = 0; e < E; e += 4) {
-          float4 w = make_float4(acc[v][e] * scale, acc[v][e + 1] * scale, acc[v][e + 2] * scale,
-                                 acc[v][e + 3] * scale);
-          *reinterpret_cast<float4*>(op + c0 + e) = w;
-        }
+        for (int e = 0; e < E; e += 4)
+          *reinterpret_cast<float4*>(op + c0 + e) = make_float4(acc[v][e] * scale, acc[v][e + 1] * scale,
+                                                                acc[v][e + 2] * scale, acc[v][e + 3] * scale);
       }
     }
   }
@@ -165,13 +317,20 @@ __global__ __launch_bounds__(256) void k_pool_fwd(const TW* __restrict__ W, cons
 template <typename TW, int G, int NV>
 hipError_t launch_t(const FwdLaunch& p, hipStream_t s) {
   dim3 grid((unsigned)((p.M + 3) / 4)), block(256);
+  FwdArgs a;
+  a.W = p.W;
+  a.offsets = p.offsets;
+  a.idx = p.idx;
+  a.B = p.B;
+  a.M = p.M;
+  a.D = p.D;
+  a.pool = p.pool;
+  a.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
+  a.out = p.out;
+  a.ro = p.ro;
   // the index type (int32 or int64) is a template argument: no per-load branch
-  if (p.idx64)
-    hipLaunchKernelGGL((k_pool_fwd<TW, G, NV, int64_t>), grid, block, 0, s, reinterpret_cast<const TW*>(p.W),
-                       p.offsets, static_cast<const int64_t*>(p.idx), p.ro, p.B, p.M, p.D, p.pool, p.out);
-  else
-    hipLaunchKernelGGL((k_pool_fwd<TW, G, NV, int32_t>), grid, block, 0, s, reinterpret_cast<const TW*>(p.W),
-                       p.offsets, static_cast<const int32_t*>(p.idx), p.ro, p.B, p.M, p.D, p.pool, p.out);
+  if (p.idx64) hipLaunchKernelGGL((k_pool_fwd<TW, G, NV, int64_t>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((k_pool_fwd<TW, G, NV, int32_t>), grid, block, 0, s, a);
   return hipGetLastError();
 }
 
