@@ -3,8 +3,10 @@
 //   g_u = sum over sorted positions k of segment u of scale_{m(k)} * G[m(k)]
 //   W_r <- opt(W_r, g_u), r = unique_keys[u]
 //
-// A row of D fp32 values is held by a group of G lanes (float4 per lane per
-// vector, NV vectors), so a wavefront works on 64/G rows at a time.
+// The lane-group form, for rows of at most 64 values (wider ones, and some of
+// these, take the wave form of reduce_wave.hip).  A row of D fp32 values is
+// held by a group of G lanes (float4 per lane per vector, NV vectors), so a
+// wavefront works on 64/G rows at a time.
 //  - Light segments (at most kChunk positions, the long tail of a skewed
 //    batch): one lane group owns the whole segment, sums its gradient rows
 //    and applies the optimizer to its table row.  Each row has exactly one
@@ -14,39 +16,11 @@
 //    row, and the block that owns the segment's first chunk adds the partials
 //    in chunk order and applies the optimizer.
 // Every sum runs in a fixed order, so results are bitwise reproducible.
-#include "emb_common.h"
-#include "kernels.h"
+#include "reduce_common.h"
 
 namespace emb {
 
 namespace {
-
-struct Upd {
-  void* W;
-  float* state;
-  int32_t D, opt, fuse;
-  float lr, eps;
-  int32_t rounding;  // bf16 stores: 0 nearest even, 1 stochastic
-  uint64_t seed;
-};
-
-struct RArgs {
-  const float* G;
-  const int32_t* seg;
-  const uint32_t* ukeys;
-  const int32_t* num_unique;
-  const int32_t* sorted_bag;  // bag of every sorted position
-  const int32_t* offsets;     // bag offsets (mean pooling scales by 1 / bag length)
-  const int32_t* chunk_seg;
-  float* grad_rows;
-  float* partials;
-  uint64_t* level2;     // [ncomb][2][D] tagged rows, cleared by the main kernel
-  uint32_t* arrivals;   // [ncomb] arrival counters, cleared by the main kernel
-  int32_t ncomb;        // combine blocks
-  void* hdr;            // workspace header (error bits)
-  int32_t N, D, pool, nchunks;
-  Upd up;
-};
 
 template <typename TW>
 struct Row4;
@@ -82,27 +56,12 @@ struct Row4<uint16_t> {
   }
 };
 
-// splitmix64 (Steele, Lea and Flood 2014): the output for generator state x
-__device__ __forceinline__ uint64_t splitmix64(uint64_t x) {
-  uint64_t z = x + 0x9e3779b97f4a7c15ull;
-  z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-  z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-  return z ^ (z >> 31);
-}
-
-// Row of four stored values with stochastic rounding to bf16: element e of
-// counter c0 + e gets the top 16 bits of splitmix64(seed ^ splitmix64(c)),
-// added to the 16 bits below the bf16 mantissa, which are then cut off (the
-// magnitude rounds up with probability dropped / 2^16); non-finite values
-// round to nearest even.
+// Row of four stored values with stochastic rounding to bf16: element e has
+// counter c0 + e
 __device__ __forceinline__ void store_bf16_stochastic(uint16_t* p, const float (&o)[4], uint64_t seed, uint64_t c0) {
   uint16_t b[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const uint32_t u = __float_as_uint(o[e]);
-    const uint32_t r16 = (uint32_t)(splitmix64(seed ^ splitmix64(c0 + (uint64_t)e)) >> 48);
-    b[e] = (u & 0x7f800000u) == 0x7f800000u ? f32_to_bf16_rne(o[e]) : (uint16_t)((u + r16) >> 16);
-  }
+  for (int e = 0; e < 4; ++e) b[e] = bf16_stochastic(o[e], seed, c0 + (uint64_t)e);
   uint2 v;
   v.x = (uint32_t)b[0] | ((uint32_t)b[1] << 16);
   v.y = (uint32_t)b[2] | ((uint32_t)b[3] << 16);
@@ -199,11 +158,34 @@ __device__ __forceinline__ void prefetch_row(const Upd& up, uint32_t r, int sub,
   }
 }
 
+// Sum of squares of a row, in every lane of its group: adjacent columns first,
+// then columns 2, 4, ... apart, the order of the wave form (reduce_wave.hip),
+// so that the unfused update equals the fused one whichever form reduced.
+template <int G, int NV>
+__device__ __forceinline__ float row_squares(const float (&acc)[NV][4]) {
+#pragma clang fp contract(off)
+  static_assert((NV & (NV - 1)) == 0, "vectors are added pairwise");
+  float s[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    s[v] = (acc[v][0] * acc[v][0] + acc[v][1] * acc[v][1]) + (acc[v][2] * acc[v][2] + acc[v][3] * acc[v][3]);
+#pragma unroll
+    for (int o = 1; o < G; o <<= 1) s[v] += __shfl_xor(s[v], o, kWave);
+  }
+#pragma unroll
+  for (int o = 1; o < NV; o <<= 1)
+#pragma unroll
+    for (int v = 0; v < NV; v += 2 * o) s[v] += s[v + o];
+  return s[0];
+}
+
 // Write g_u (if grad_rows) and apply the optimizer to row r (if fused) from
 // the prefetched row.  Called by the G lanes of one group, all active.
 template <typename TW, int G, int NV>
 __device__ __forceinline__ void apply_row(const Upd& up, float* grad_rows, int64_t u, uint32_t r,
                                           const float (&acc)[NV][4], const RowPre<NV>& pre, int sub) {
+  // (fused products are written out, as in the wave form)
+#pragma clang fp contract(off)
   const int D = up.D;
   if (grad_rows) {
     float* gp = grad_rows + u * D;
@@ -216,14 +198,8 @@ __device__ __forceinline__ void apply_row(const Upd& up, float* grad_rows, int64
   if (!up.fuse) return;
   float step = up.lr;
   if (up.opt == EMB_OPT_ADAGRAD_ROWWISE) {
-    float sq = 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) sq += acc[v][e] * acc[v][e];
-#pragma unroll
-    for (int o = 1; o < G; o <<= 1) sq += __shfl_xor(sq, o, kWave);
-    const float h = pre.h + sq / (float)D;
+    // (columns past the row's end hold zeros)
+    const float h = pre.h + row_squares<G, NV>(acc) / (float)D;
     if (sub == 0) up.state[r] = h;
     step = up.lr / (sqrtf(h) + up.eps);
   }
@@ -244,7 +220,7 @@ __device__ __forceinline__ void apply_row(const Upd& up, float* grad_rows, int64
         float w[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          hv[v][e] += acc[v][e] * acc[v][e];
+          hv[v][e] = __builtin_fmaf(acc[v][e], acc[v][e], hv[v][e]);
           w[e] = pre.w[v][e] - up.lr * acc[v][e] / (sqrtf(hv[v][e]) + up.eps);
         }
         Row4<float>::store(hp + c0, hv[v]);
@@ -259,7 +235,7 @@ __device__ __forceinline__ void apply_row(const Upd& up, float* grad_rows, int64
     if (c0 < D) {
       float w[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) w[e] = pre.w[v][e] - step * acc[v][e];
+      for (int e = 0; e < 4; ++e) w[e] = __builtin_fmaf(-step, acc[v][e], pre.w[v][e]);
       store_w<TW>(up, wp + c0, w, (uint64_t)r * (uint64_t)D + (uint64_t)c0);
     }
   }
@@ -271,60 +247,6 @@ __device__ __forceinline__ void finalize(const Upd& up, float* grad_rows, int64_
   RowPre<NV> pre;
   prefetch_row<TW, G, NV>(up, r, sub, pre);
   apply_row<TW, G, NV>(up, grad_rows, u, r, acc, pre, sub);
-}
-
-// whether the dedup this reduce follows flagged an error: its unique scan made
-// its generation the header's, so its error bits are those of that generation
-__device__ __forceinline__ bool dedup_failed(const RArgs& a) {
-  const WsHeader* h = reinterpret_cast<const WsHeader*>(a.hdr);
-  return (call_errors(h, h->gen) & kDedupErrors) != 0u;
-}
-
-// 1 / bag length for mean pooling (a position's bag is never empty), else 1
-__device__ __forceinline__ float bag_scale(const RArgs& a, int bag) {
-  return a.pool == EMB_POOL_MEAN ? 1.0f / (float)(a.offsets[bag + 1] - a.offsets[bag]) : 1.0f;
-}
-
-// Metadata of one heavy-segment check: the pieces of heavy segments that
-// lie in chunk c.  Slot 0: the segment holding the chunk's first position
-// (if heavy); slot 1: a different heavy segment holding its last position.
-struct ChunkPieces {
-  int lo[2], hi[2];
-  int u0, s0, e0;  // the segment holding the chunk's first position
-  int u1, s1, e1;  // the segment holding the chunk's last position
-};
-
-__device__ __forceinline__ ChunkPieces chunk_pieces(const RArgs& a, int c, int U) {
-  ChunkPieces r;
-  const int p0 = c * kChunk, p1 = min(a.N, p0 + kChunk);
-  const int u0 = a.chunk_seg[c], cs1 = a.chunk_seg[c + 1];
-  // all needed offsets in one round of independent loads
-  const int s0 = a.seg[u0], e0 = a.seg[u0 + 1];
-  const int sc = a.seg[cs1];
-  const int scm = cs1 > 0 ? a.seg[cs1 - 1] : 0;
-  const int scp = cs1 < U ? a.seg[cs1 + 1] : a.N;
-  if (sc == p1) {  // position p1 starts segment cs1: the chunk ends with segment cs1 - 1
-    r.u1 = cs1 - 1;
-    r.s1 = scm;
-    r.e1 = sc;
-  } else {
-    r.u1 = cs1;
-    r.s1 = sc;
-    r.e1 = scp;
-  }
-  r.u0 = u0;
-  r.s0 = s0;
-  r.e0 = e0;
-  r.lo[0] = r.hi[0] = r.lo[1] = r.hi[1] = 0;
-  if (e0 - s0 > kChunk) {
-    r.lo[0] = p0;
-    r.hi[0] = min(p1, e0);
-  }
-  if (r.u1 != u0 && r.e1 - r.s1 > kChunk) {
-    r.lo[1] = r.s1;
-    r.hi[1] = p1;
-  }
-  return r;
 }
 
 // Sum of the scaled gradient rows of sorted positions [lo, hi) (at most 64)
@@ -545,8 +467,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(reduce_wave
 // and applies the optimizer.  The order of every sum is fixed, so the result
 // does not depend on which block arrives last; no block ever waits for
 // another to arrive.
-constexpr uint32_t kLevel2Tag = 1u;  // rows and counters are cleared by the main kernel
-
 // sum of this lane's columns of level-2 rows [g0, g1) (slot 1 of the first
 // range, slot 0 of the others), rows split over the lane groups with the
 // words of several rows loaded together; a word is polled until it carries
@@ -690,15 +610,6 @@ __global__ __launch_bounds__(kCombineThreads) void k_reduce_combine(RArgs a) {
   }
 }
 
-struct UArgs {
-  const float* grad_rows;
-  const uint32_t* ukeys;
-  const int32_t* num_unique;
-  int32_t max_unique;
-  uint32_t rows;
-  Upd up;
-};
-
 template <typename TW, int G, int NV>
 __global__ __launch_bounds__(256) void k_sparse_update(UArgs a) {
   constexpr int RPI = kWave / G;
@@ -728,8 +639,8 @@ hipError_t launch_reduce_t(const RArgs& ra, int blocks_main, int blocks_comb, hi
 // Rows of 33 to 64 values are held two vectors per lane (half as many lanes
 // per row, twice as many rows per wavefront): a wavefront then carries twice
 // the light segments, which outweighs the lower occupancy (measured on rows
-// of 64 fp32 values).  Narrower rows, and wider ones (128 bf16 values lost on
-// small batches), keep one vector.
+// of 64 fp32 values).  Narrower rows keep one vector; wider ones take the wave
+// form.
 template <typename TW>
 hipError_t launch_reduce_dt(const RArgs& ra, int bm, int bc, hipStream_t s) {
   const int vecs = (ra.D + 3) / 4;
@@ -738,10 +649,6 @@ hipError_t launch_reduce_dt(const RArgs& ra, int bm, int bc, hipStream_t s) {
   if (vecs <= 4) return launch_reduce_t<TW, 4, 1>(ra, bm, bc, s);
   if (vecs <= 8) return launch_reduce_t<TW, 8, 1>(ra, bm, bc, s);
   if (vecs <= 16) return launch_reduce_t<TW, 8, 2>(ra, bm, bc, s);
-  if (vecs <= 32) return launch_reduce_t<TW, 32, 1>(ra, bm, bc, s);
-  if (vecs <= 64) return launch_reduce_t<TW, 64, 1>(ra, bm, bc, s);
-  if (vecs <= 128) return launch_reduce_t<TW, 64, 2>(ra, bm, bc, s);
-  if (vecs <= 256) return launch_reduce_t<TW, 64, 4>(ra, bm, bc, s);
   return hipErrorInvalidValue;
 }
 
@@ -751,8 +658,8 @@ hipError_t launch_update_t(const UArgs& ua, int blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
-// the reduce's lane layout for every width, so that the row-wise Adagrad sum
-// of squares runs in the same order and the unfused update equals the fused one
+// (wider rows: launch_update_wave; the row-wise Adagrad sum of squares runs in
+// one order in every form, so the unfused update equals the fused one)
 template <typename TW>
 hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
   const int vecs = (ua.up.D + 3) / 4;
@@ -760,12 +667,27 @@ hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
   if (vecs <= 2) return launch_update_t<TW, 2, 1>(ua, blocks, s);
   if (vecs <= 4) return launch_update_t<TW, 4, 1>(ua, blocks, s);
   if (vecs <= 8) return launch_update_t<TW, 8, 1>(ua, blocks, s);
-  if (vecs <= 16) return launch_update_t<TW, 8, 2>(ua, blocks, s);
-  if (vecs <= 32) return launch_update_t<TW, 32, 1>(ua, blocks, s);
-  if (vecs <= 64) return launch_update_t<TW, 64, 1>(ua, blocks, s);
-  if (vecs <= 128) return launch_update_t<TW, 64, 2>(ua, blocks, s);
-  if (vecs <= 256) return launch_update_t<TW, 64, 4>(ua, blocks, s);
   return hipErrorInvalidValue;
+}
+
+// Which form reduces.  Rows of at most 32 values: lane groups (a wavefront
+// would leave half its lanes idle).  Rows of more than 64: the wave form at
+// every size (128 bf16 values, 5.5M lookups: 510 -> 318 us; 256 fp32 values,
+// 18k lookups: 62 -> 17).  Between, with row-wise Adagrad on one table (main
+// kernel and combine, lane groups -> wave form, us; ids uniform / Zipf 0.9 /
+// 1.05 / 1.2):
+//    30k lookups   14.5 -> 11.7   20.0 -> 12.4   19.3 -> 14.6   14.3 -> 14.9
+//   120k           23.6 -> 19.0   29.0 -> 22.4   20.8 -> 19.6   17.0 -> 17.7
+//   480k           59.7 -> 52.5   53.4 -> 46.6   37.6 -> 38.2   28.8 -> 33.2
+//   720k           84.2 -> 77.1   70.3 -> 64.7   48.6 -> 46.9   36.3 -> 40.5
+//   1.2M          154.1 -> 123.1 110.4 -> 94.8   70.6 -> 65.5   52.5 -> 55.9
+// The wave form wins by its loads in flight and loses, on the most skewed ids
+// (many rows of G in the L2s), by its instructions per row.  The 50M-row
+// workload (Zipf 1.2, 492k lookups) would lose 3 us; the 8-table one (Zipf
+// 1.1, 836k) gains 8.
+constexpr int kWaveFormFew = 2048, kWaveFormMany = 10240;
+bool wave_form(int D, int nchunks) {
+  return D > 64 || (D > kLaneGroupDim && (nchunks <= kWaveFormFew || nchunks > kWaveFormMany));
 }
 
 int clamp_blocks(int64_t want, int lo, int hi) {
@@ -808,6 +730,7 @@ hipError_t launch_grad_reduce(const ReduceLaunch& p, hipStream_t s) {
   ra.up.eps = p.eps;
   ra.up.rounding = p.rounding;
   ra.up.seed = p.seed;
+  if (wave_form(p.D, ra.nchunks)) return launch_reduce_wave(ra, p.dtype, s);
   // main: two wavefronts per chunk of sorted positions (one for its heavy
   // pieces, one for a batch of light segments), up to two full devices
   const int bm = clamp_blocks(((int64_t)ra.nchunks + 1) / 2, 1, 4096);
@@ -832,6 +755,7 @@ hipError_t launch_sparse_update(const UpdateLaunch& p, hipStream_t s) {
   ua.up.eps = p.eps;
   ua.up.rounding = p.rounding;
   ua.up.seed = p.seed;
+  if (p.D > kLaneGroupDim) return launch_update_wave(ua, p.dtype, s);
   const int blocks = clamp_blocks((p.max_unique + 15) / 16, 1, 2048);
   return p.dtype == EMB_FP32 ? launch_update_dt<float>(ua, blocks, s) : launch_update_dt<uint16_t>(ua, blocks, s);
 }

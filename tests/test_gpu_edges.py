@@ -63,3 +63,81 @@ def test_forward_short_and_long_bags(dtype, D, B):
     ro = np.concatenate([[0], np.cumsum(rows)])
     for idx64 in (False, True):
         parity.run_case(ro, W, off, idx, G, B, "sum", "sgd", 0.5, 0.0, exact=dtype == "fp32", idx64=idx64)
+
+
+def _segments_case(rng, seg_lens, M, repeat):
+    """A one-table batch of M bags whose sorted keys have the given segment
+    lengths; `repeat` positions of a bag carry the same id in a row."""
+    N = int(sum(seg_lens))
+    ids = np.repeat(np.arange(len(seg_lens)), seg_lens)
+    if repeat > 1:
+        # whole groups of equal ids move together, so bags hold runs of one id
+        groups = [g for L in np.split(ids, np.flatnonzero(np.diff(ids)) + 1)
+                  for g in np.array_split(L, max(1, len(L) // repeat))]
+        ids = np.concatenate([groups[i] for i in rng.permutation(len(groups))])
+    else:
+        ids = ids[rng.permutation(N)]
+    cuts = np.sort(rng.integers(0, N + 1, size=M - 1))
+    off = np.concatenate([[0], cuts, [N]]).astype(np.int32)
+    return off, ids.astype(np.int32)
+
+
+_SEGMENTS = {
+    "one": [1],
+    "chunk": [64],
+    "past a chunk": [65],
+    "two long": [65, 65],
+    "single positions": [1] * 130,
+    "ends at chunk ends": [64, 32, 32, 16, 48, 1, 63],
+    "crossing": [40, 40, 40, 64, 64, 2, 63, 64, 1, 65, 15, 17, 16],
+    "long after short": [3, 200, 5, 128, 64, 64, 129, 1, 1, 500, 60, 7],
+    "across combine ranges": [10, 64 * 64 * 2 + 100, 3, 64 * 64 + 1, 64, 50],
+}
+
+
+@pytest.mark.parametrize("dtype,D", [("fp32", 36), ("fp32", 64), ("bf16", 40), ("fp32", 68), ("fp32", 128),
+                                     ("bf16", 104), ("fp32", 256), ("bf16", 264), ("fp32", 1024)])
+@pytest.mark.parametrize("name", sorted(_SEGMENTS))
+def test_reduce_segment_lengths(dtype, D, name):
+    """Segments ending at, before and after the boundaries of chunks, of a
+    chunk's parts and of combine ranges, with and without repeated bags; the
+    gradient rows are integers, their sums below 2^24, so every order agrees
+    bit for bit (fp32 tables: the updated rows too, lr a power of two)."""
+    print(f"case reduce segments {name} {dtype} D={D}", flush=True)
+    rng = np.random.default_rng(D + len(name))
+    for repeat in (1, 5):
+        M = max(1, sum(_SEGMENTS[name]) // 9)
+        off, idx = _segments_case(rng, _SEGMENTS[name], M, repeat)
+        R = len(_SEGMENTS[name]) + 3
+        W = _dyadic(rng, (R, D), dtype)
+        G = rng.integers(-16, 17, size=(M, D)).astype(np.float32)
+        parity.run_case([0, R], W, off, idx, G, M, "sum", "sgd", 0.5, 0.0, exact=dtype == "fp32")
+        # unfused, and every optimizer, within the parity tolerance; the unfused
+        # update equals the fused one bit for bit
+        if repeat == 5:
+            for opt in ("adagrad", "adagrad_ew"):
+                s0 = np.full(R if opt == "adagrad" else (R, D), 1.0, np.float32)
+                got = [parity.run_case([0, R], W, off, idx, G, M, "mean", opt, 0.01, 1e-8, state0=s0.copy(),
+                                       fused=fused) for fused in (True, False)]
+                keys = got[0][0].unique_keys
+                np.testing.assert_array_equal(got[0][2].rows(keys), got[1][2].rows(keys))
+                np.testing.assert_array_equal(got[0][2].state_rows(keys), got[1][2].state_rows(keys))
+
+
+@pytest.mark.parametrize("D", [36, 48, 64])
+@pytest.mark.parametrize("n", [2048 * 64, 2048 * 64 + 1, 10240 * 64 + 1])
+def test_unfused_equals_fused_in_both_forms(D, n):
+    """Batches on both sides of the sizes where rows of 33 to 64 values change
+    the form of their reduce; the separate update has one form."""
+    print(f"case unfused forms D={D} N={n}", flush=True)
+    rng = np.random.default_rng(n + D)
+    rows, B = 30000, n // 20
+    cuts = np.sort(rng.integers(0, n + 1, size=B - 1))
+    off = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    idx = ((rng.zipf(1.2, size=n) - 1) % rows).astype(np.int32)
+    W = rng.uniform(-0.1, 0.1, size=(rows, D)).astype(np.float32)
+    G = rng.standard_normal((B, D)).astype(np.float32)
+    got = [parity.run_case([0, rows], W, off, idx, G, B, "sum", "adagrad", 0.01, 1e-8, fused=f) for f in (True, False)]
+    keys = got[0][0].unique_keys
+    np.testing.assert_array_equal(got[0][2].rows(keys), got[1][2].rows(keys))
+    np.testing.assert_array_equal(got[0][2].state_rows(keys), got[1][2].state_rows(keys))
