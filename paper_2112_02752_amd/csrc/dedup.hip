@@ -4,7 +4,8 @@
 //   perm     = stable ascending sort of positions by key
 //   unique_keys / seg_offsets / counts = the runs of equal sorted keys
 //
-// Kernels, in stream order:
+// (Batches of a few thousand keys are deduplicated by one workgroup:
+// dedup_small.hip.)  Kernels, in stream order:
 //  1. k_sort_pass (once per digit): a tile ranks its keys with wavefront
 //     ballots (the lanes sharing a digit are found with one ballot per digit
 //     bit, the rank is a masked popcount), reorders them in LDS by digit and
@@ -670,12 +671,11 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
 #pragma unroll
   for (int i = 0; i < IT; ++i) {
     const bool valid = wbase + i * kWave + lane < a.N;
-    uint64_t peers = __ballot(valid);
-    for (int b = 0; b < a.bits; ++b) {
-      const bool bit = (dig[i] >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      peers &= bit ? bb : ~bb;
-    }
+    const uint64_t all = __ballot(valid);
+    uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+#pragma unroll
+    for (int b = 0; b < RB; ++b) keep_peers(dig[i], b, lo, hi);  // (a.bits is RB)
+    const uint64_t peers = ((uint64_t)hi << 32) | lo;
     lrank[i] = 0;
     if (valid) {
       const uint32_t r = lanes_below(peers);
@@ -1260,6 +1260,7 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
     hipLaunchKernelGGL(k_unique_empty, dim3(1), dim3(64), 0, s, p.num_unique, p.seg_offsets);
     return hipGetLastError();
   }
+  if (dedup_is_small(p.N, p.M)) return launch_dedup_small(p, s);
   const int N = (int)p.N;
   const int uniq_tiles = (N + kUniqTile - 1) / kUniqTile;
   const int nchunks = (N + kChunk - 1) / kChunk;

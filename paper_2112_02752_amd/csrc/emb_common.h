@@ -173,6 +173,12 @@ struct TableOffsets {
   uint32_t off[EMB_MAX_TABLES + 1];
 };
 
+// Batches deduplicated by one workgroup: keys that fit its LDS, and bags few
+// enough to be read by it (bags may be empty, so their number is not bounded by
+// the keys').
+constexpr int kSmallKeys = 8192;
+constexpr int kSmallBags = 32768;
+
 // Routing: ranks of a sharding, their first global rows (by value in kernel
 // arguments), bags one routing block covers at most, positions it aims at,
 // threads of a per-rank scan block.
@@ -212,6 +218,15 @@ __device__ __forceinline__ void hist_add(uint32_t* hist, uint32_t d, bool valid,
 // number of set bits of `mask` below this lane
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+}
+
+// lo, hi: lanes that may share this lane's digit; those whose bit b of it
+// differs leave
+__device__ __forceinline__ void keep_peers(uint32_t d, int b, uint32_t& lo, uint32_t& hi) {
+  const int32_t m = (int32_t)(d << (31 - b)) >> 31;  // all ones where the bit is set
+  const uint64_t bb = __ballot(m < 0);
+  lo &= ~((uint32_t)bb ^ (uint32_t)m);
+  hi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)m);
 }
 
 // device-coherent (agent scope) loads and stores of words other workgroups
@@ -305,24 +320,32 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// inclusive wave scan (sum) of a 32-bit value
+// Value of the lane a DPP control names; 0 where it names none or `ROWS` (a
+// mask of the wavefront's four rows of 16 lanes) leaves the row out.
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
+}
+// Inclusive scans of a 32-bit value over the wavefront: within rows of 16
+// lanes by shifts of 1, 2, 4 and 8, then the rows' last lanes carried on (no
+// trip through LDS, whose latency each of six shuffles would wait for).
 __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, kWave);
-    if (lane >= o) v += t;
-  }
+  v += dpp_or_zero<0x111>(v);
+  v += dpp_or_zero<0x112>(v);
+  v += dpp_or_zero<0x114>(v);
+  v += dpp_or_zero<0x118>(v);
+  v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
   return v;
 }
 
 __device__ __forceinline__ uint32_t wave_incl_max(uint32_t v) {
-  const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    uint32_t t = __shfl_up(v, o, kWave);
-    if (lane >= o) v = v > t ? v : t;
-  }
+  v = max(v, dpp_or_zero<0x111>(v));
+  v = max(v, dpp_or_zero<0x112>(v));
+  v = max(v, dpp_or_zero<0x114>(v));
+  v = max(v, dpp_or_zero<0x118>(v));
+  v = max(v, dpp_or_zero<0x142, 0xa>(v));
+  v = max(v, dpp_or_zero<0x143, 0xc>(v));
   return v;
 }
 

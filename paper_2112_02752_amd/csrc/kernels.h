@@ -48,6 +48,9 @@ struct DedupLaunch {
   int32_t waitfree;
 };
 hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s);
+// the same by one workgroup, for the batches dedup_is_small admits
+bool dedup_is_small(int64_t N, int64_t M);
+hipError_t launch_dedup_small(const DedupLaunch& p, hipStream_t s);
 
 // A group dedup: the batches of a group sorted as one, each key carrying its
 // batch's index above the key bits, then each batch's share split off into

@@ -141,3 +141,26 @@ def test_unfused_equals_fused_in_both_forms(D, n):
     keys = got[0][0].unique_keys
     np.testing.assert_array_equal(got[0][2].rows(keys), got[1][2].rows(keys))
     np.testing.assert_array_equal(got[0][2].state_rows(keys), got[1][2].state_rows(keys))
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1025, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("rows,B", [([2], None), ([1], None), ([70_000], 32768), ([300, 1, 5000], None),
+                                    ([9] * 40, 1), ([1 << 20, 1 << 20, 40], 2)])
+def test_dedup_of_small_batches(n, rows, B):
+    """Batches on both sides of the sizes one workgroup deduplicates, one and
+    several tables, one bag a table, and more bags than ids (most of them
+    empty); integer outputs are exact (int32 and int64 ids)."""
+    T = len(rows)
+    B = max(1, n // (3 * T)) if B is None else B
+    M = T * B
+    print(f"case small dedup N={n} T={T} B={B}", flush=True)
+    rng = np.random.default_rng(n + T)
+    cuts = np.sort(rng.integers(0, n + 1, size=M - 1)) if M > 1 else np.zeros(0, np.int64)
+    off = np.concatenate([[0], cuts, [n]]).astype(np.int32)
+    bag = np.repeat(np.arange(M), np.diff(off))
+    per = np.asarray(rows)[bag // B]
+    idx = np.minimum((per * rng.random(n) ** 3).astype(np.int64), per - 1).astype(np.int32)
+    W = _dyadic(rng, (sum(rows), 4), "fp32")
+    G = (rng.integers(-8, 9, size=(M, 4)) / 8.0).astype(np.float32)
+    ro = np.concatenate([[0], np.cumsum(rows)])
+    parity.run_case(ro, W, off, idx, G, B, "sum", "sgd", 0.5, 0.0, exact=True, idx64=bool(n % 2))
