@@ -13,14 +13,15 @@
 //     comes from one of two schemes.  When every tile of a pass is resident
 //     at once, the tile publishes its digit counts (an LDS histogram) as soon
 //     as its keys are loaded, and prefix blocks launched after the tiles sum
-//     the published counts and publish final offsets while the tiles rank;
-//     the first pass also finds each position's bag.  Otherwise k_prepare
-//     first writes every position's bag id (and key, for several tables), and
-//     each pass is preceded by k_tile_counts (every tile's digit counts) and
-//     k_column_scan (per digit, the prefix of those counts over the tiles,
-//     and the digit's total), so that the pass reads its offsets with no
-//     wait.  Ranks follow position order within a tile and tiles follow
-//     position order, so every pass is stable and so is the whole sort.
+//     the published counts and publish final offsets while the tiles rank.
+//     Otherwise each pass is preceded by k_tile_counts (every tile's digit
+//     counts) and k_column_scan (per digit, the prefix of those counts over the
+//     tiles, and the digit's total), so that the pass reads its offsets with no
+//     wait.  The first pass reads the ids, finds each position's bag and adds
+//     its table's first row (a kernel of its own for bags and keys took 34 us
+//     for 5.5M ids of 26 tables; the first pass takes 5 to 10 us more).  Ranks
+//     follow position order within a tile and tiles follow position order, so
+//     every pass is stable and so is the whole sort.
 //  2. k_unique: head flags key[k] != key[k-1], a block scan plus a look-back
 //     of (number of heads, last head position) gives every head its segment
 //     index and the length of the previous segment; when its tiles are not
@@ -54,18 +55,7 @@ constexpr uint64_t kFlagAgg = 1, kFlagInc = 2;
 
 // ------------------------------------------------------------------ prepare
 
-struct PrepArgs {
-  const int32_t* offsets;
-  const void* idx;
-  int32_t idx64;
-  TableOffsets ro;
-  int32_t B, M, bags_per_block;
-  uint32_t* keys_out;  // null for int32 ids of one table (the ids are the keys)
-  int32_t* bag_of;
-  uint32_t key_hi;     // or-ed into every key (a group dedup's batch index bits; 0 otherwise)
-};
-
-// Used when the tiles of a pass are not all resident at once.  A block owns a
+// Keys and bags of a group dedup's batches, before its passes.  A block owns a
 // contiguous range of bags and therefore of positions.  The bags' offsets are
 // staged in LDS; every thread takes positions of the range in strides, finds
 // each one's bag by a binary search in LDS, and writes the bag id (and the key
@@ -107,11 +97,6 @@ __device__ __forceinline__ void prepare_block(const A& a, int block, int32_t* s_
   }
 }
 
-__global__ __launch_bounds__(kPrepThreads) void k_prepare(PrepArgs a) {
-  __shared__ int32_t s_off[kPrepMaxBags + 1];
-  prepare_block(a, blockIdx.x, s_off);
-}
-
 // ------------------------------------------------------------- sort pass
 
 struct PassArgs {
@@ -136,6 +121,7 @@ struct PassArgs {
   int32_t idx64;
   TableOffsets ro;
   int32_t B, M, T;
+  uint32_t b_magic;        // floor(2^32 / B) (B > 1)
   uint64_t* uniq_status;
   int32_t uniq_tiles;
   int32_t N, ntiles, shift, bits, pass, status_stride;
@@ -410,15 +396,14 @@ __device__ __forceinline__ void sort_prefix_range(const PassArgs& a, uint32_t gc
 // Bag of each of this thread's positions of a tile: the bag holding position
 // j is the last m with offsets[m] <= j.  One offset in every S (S chosen so
 // the samples fit one per thread) narrows the tile's bags to a few sample
-// intervals whose offsets are staged in LDS.  Every nonempty staged bag that
-// overlaps the tile writes its id at its first position in the tile, and an
-// inclusive max-scan over the tile's positions carries each id forward to
-// the bag's other positions (bag ids grow with position).  Intervals that do
-// not fit the stage are searched in global memory.  `s_work` holds
-// one int per position of the tile.
+// intervals.  Every nonempty bag of these that overlaps the tile writes its id
+// at its first position in the tile, and an inclusive max-scan over the tile's
+// positions carries each id forward to the bag's other positions (bag ids grow
+// with position).  Intervals of more than kBagMarks bags (most of them empty)
+// are searched instead.  `s_work` holds one int per position of the tile.
 template <int IT>
-__device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int32_t* s_boff, int* s_lohi,
-                                               int32_t* s_work, uint32_t* s_wmax, int32_t (&bag)[IT]) {
+__device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int* s_lohi, int32_t* s_work,
+                                               uint32_t* s_wmax, int32_t (&bag)[IT]) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
   const int64_t p0 = (int64_t)tile * (kSortThreads * IT);
   const int64_t p1 = min(p0 + (kSortThreads * IT), (int64_t)a.N);
@@ -427,6 +412,8 @@ __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int3
   int samp = 0;
   if (tid < nsamp) samp = a.offsets[min(tid * S, a.M)];
   if (tid == 0) s_lohi[0] = s_lohi[1] = 0;
+  // ids are stored plus one, so that 0 means "no bag starts here"
+  for (int i = tid; i < (kSortThreads * IT); i += kSortThreads) s_work[i] = 0;
   __syncthreads();
   // samples are nondecreasing: count those <= p0 and <= p1 - 1
   const uint64_t le0 = __ballot(tid < nsamp && samp <= p0);
@@ -439,14 +426,20 @@ __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int3
   const int m_lo = (s_lohi[0] - 1) * S;                    // a bag at or before the tile's first bag
   const int m_hi = min((s_lohi[1] - 1) * S + S, a.M);      // an offset index at or after its last bag's end
   const int nst = m_hi - m_lo + 1;
-  if (nst <= kBagStage + 1) {
-    for (int i = tid; i < nst; i += kSortThreads) s_boff[i] = a.offsets[m_lo + i];
-    // ids are stored plus one, so that 0 means "no bag starts here"
-    for (int i = tid; i < (kSortThreads * IT); i += kSortThreads) s_work[i] = 0;
-    __syncthreads();
-    for (int i = tid; i < nst - 1; i += kSortThreads) {
-      const int64_t st = s_boff[i], en = s_boff[i + 1];
-      if (st < en && st < p1 && en > p0) s_work[(st > p0 ? st : p0) - p0] = m_lo + i + 1;
+  if (nst <= kBagMarks) {
+    constexpr int UN = 4;
+    for (int i0 = tid; i0 < nst - 1; i0 += UN * kSortThreads) {
+      int32_t st[UN], en[UN];
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const int i = i0 + u * kSortThreads;
+        st[u] = i < nst - 1 ? a.offsets[m_lo + i] : 0;
+        en[u] = i < nst - 1 ? a.offsets[m_lo + i + 1] : 0;
+      }
+#pragma unroll
+      for (int u = 0; u < UN; ++u)
+        if (st[u] < en[u] && st[u] < p1 && en[u] > p0)
+          s_work[(st[u] > p0 ? st[u] : p0) - p0] = m_lo + i0 + u * kSortThreads + 1;
     }
     __syncthreads();
     uint32_t v[IT];
@@ -509,8 +502,7 @@ __device__ inline int xcd_tile(int b, int n) {
 //   [tstart] the tile's digit starts [ND], [gbase] digit bases [ND]
 //   [keys]   reorder buffer [TILE]: keys, then bags; before the reorder the
 //            bag search's per-position work area
-//   [vals]   reorder buffer [TILE]: values; before the reorder the bag
-//            search's staged offsets
+//   [vals]   reorder buffer [TILE]: values, then bags
 // Before the ranking [cnt]..[gbase] hold the co-resident pass's published
 // histograms (u32 [kMaxPasses][ND]).  A prefix block uses the arena from its
 // start for its in-group prefixes and digit bases.
@@ -524,8 +516,7 @@ struct PassLds {
   static constexpr int kGbase = kTstart + ND * 4;
   static constexpr int kKeys = kGbase + ND * 4;
   static constexpr int kVals = kKeys + TILE * 4;
-  static constexpr int kValsWords = TILE > kBagStage + 1 ? TILE : kBagStage + 1;
-  static constexpr int kTileBytes = kVals + kValsWords * 4;
+  static constexpr int kTileBytes = kVals + TILE * 4;
   static constexpr int kPrefixBytes = ((kPrefixGroup / 2) * ND + ND) * 4;
   static constexpr int kRangeBytes = (ND + kSortThreads) * 4;
   static constexpr int kBytes0 = kTileBytes > kPrefixBytes ? kTileBytes : kPrefixBytes;
@@ -639,11 +630,14 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
       for (int i = 0; i < IT; ++i) dig[i] = (key[i] >> a.shift) & mask;
       publish_counts();
     }
-    find_tile_bags<IT>(a, tile, s_vals, s_lohi, reinterpret_cast<int32_t*>(s_keys), s_wsum, bag);
+    find_tile_bags<IT>(a, tile, s_lohi, reinterpret_cast<int32_t*>(s_keys), s_wsum, bag);
     if (!one_table) {
 #pragma unroll
       for (int i = 0; i < IT; ++i) {
-        key[i] += s_toff[bag[i] / a.B];
+        // the division by B as a multiplication, one too few at most
+        uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag[i], a.b_magic) : (uint32_t)bag[i];
+        if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag[i]) ++t;
+        key[i] += s_toff[t];
         dig[i] = (key[i] >> a.shift) & mask;
       }
       publish_counts();
@@ -814,25 +808,49 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
 // the pass itself, which reads its tile's offsets with no wait.
 
 struct CountArgs {
-  const uint32_t* keys;
+  const uint32_t* keys;    // null: the first pass, keys from the ids
   int32_t N, shift, bits, stride;
   uint32_t* counts;  // [tiles][stride]
+  // first pass: ids, and the tables' first rows and first positions
+  const void* idx;
+  int32_t idx64, B, T;
+  const int32_t* offsets;
+  TableOffsets ro;
 };
 
 template <int IT>
 __global__ __launch_bounds__(kSortThreads) void k_tile_counts(CountArgs a) {
   __shared__ uint32_t s_hist[kMaxDigits];
+  __shared__ int32_t s_first[EMB_MAX_TABLES];  // first position of each table
+  __shared__ uint32_t s_toff[EMB_MAX_TABLES];
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
   const int nd = 1 << a.bits;
   const uint32_t mask = (uint32_t)nd - 1u;
-  for (int i = tid; i < nd; i += kSortThreads) s_hist[i] = 0u;
-  __syncthreads();
   const int64_t wbase = (int64_t)blockIdx.x * (kSortThreads * IT) + w * (kWave * IT);
   uint32_t key[IT];
 #pragma unroll
   for (int i = 0; i < IT; ++i) {
     const int64_t pos = wbase + i * kWave + lane;
-    key[i] = pos < a.N ? a.keys[pos] : 0u;
+    key[i] = pos < a.N ? (a.keys ? a.keys[pos] : (uint32_t)load_id(a.idx, a.idx64, pos)) : 0u;
+  }
+  for (int i = tid; i < nd; i += kSortThreads) s_hist[i] = 0u;
+  const bool tables = !a.keys && a.T > 1;
+  if (tables && tid < a.T) {
+    s_first[tid] = a.offsets[(int64_t)tid * a.B];
+    s_toff[tid] = a.ro.off[tid];
+  }
+  __syncthreads();
+  if (tables) {
+    // a position's table: the last whose first position is not after it (an
+    // empty table shares its first position with the next one)
+#pragma unroll
+    for (int i = 0; i < IT; ++i) {
+      const int64_t pos = wbase + i * kWave + lane;
+      int t = 0;
+      for (int step = EMB_MAX_TABLES / 2; step > 0; step >>= 1)
+        if (t + step < a.T && s_first[t + step] <= pos) t += step;
+      key[i] += s_toff[t];
+    }
   }
 #pragma unroll
   for (int i = 0; i < IT; ++i) hist_add(s_hist, (key[i] >> a.shift) & mask, wbase + i * kWave + lane < a.N, lane);
@@ -848,37 +866,54 @@ struct ColScanArgs {
 
 // One block per kColDigits digits; thread (digit, chunk of consecutive
 // tiles): the chunk's counts are loaded kColBatch at a time, the chunk sums
-// scanned in LDS, and the chunk rewritten with running prefixes.
-constexpr int kColDigits = 16;
-constexpr int kColChunks = 64;
+// scanned across the block, and the chunk rewritten with running prefixes (from
+// registers where it is one batch: up to 2048 tiles, 8M keys).  Bound by the
+// latency of its loads and the blocks at work: with 16 digits a block, two
+// loads of every count and the sums added one by one it took 11 us for 1340
+// tiles of 256 to 512 digits (16 to 32 blocks).
+constexpr int kColDigits = 8;
+constexpr int kColChunks = 128;
 constexpr int kColBatch = 16;
 __global__ __launch_bounds__(kColDigits * kColChunks) void k_column_scan(ColScanArgs a) {
-  __shared__ uint32_t s_cs[kColChunks][kColDigits];
+  constexpr int NWd = kColChunks / kWave;  // wavefronts that scan one digit's chunk sums
+  __shared__ uint32_t s_cs[kColDigits][kColChunks + 1];
+  __shared__ uint32_t s_w[kColDigits * NWd];
   const int tid = threadIdx.x, dl = tid % kColDigits, c = tid / kColDigits;
   const int d = blockIdx.x * kColDigits + dl;
   const int ct = (a.tiles + kColChunks - 1) / kColChunks;
   const int t0 = min(a.tiles, c * ct), t1 = min(a.tiles, t0 + ct);
   const bool ok = d < a.nd;
-  uint32_t sum = 0;
-  for (int tb = t0; tb < t1; tb += kColBatch) {
-    uint32_t v[kColBatch];
+  uint32_t v[kColBatch];
+  auto load_batch = [&](int tb) {
 #pragma unroll
     for (int i = 0; i < kColBatch; ++i) v[i] = ok && tb + i < t1 ? a.counts[(size_t)(tb + i) * a.stride + d] : 0u;
+  };
+  uint32_t sum = 0;
+#pragma unroll 1
+  for (int tb = t0; tb < t1; tb += kColBatch) {
+    load_batch(tb);
 #pragma unroll
     for (int i = 0; i < kColBatch; ++i) sum += v[i];
   }
-  s_cs[c][dl] = sum;
+  s_cs[dl][c] = sum;
   __syncthreads();
-  uint32_t run = 0, total = 0;
-  for (int cc = 0; cc < kColChunks; ++cc) {
-    if (cc < c) run += s_cs[cc][dl];
-    total += s_cs[cc][dl];
+  {
+    // the sums of digit sd's chunks, one a thread
+    const int sd = tid / kColChunks, sc = tid % kColChunks, w = tid / kWave;
+    const uint32_t x = s_cs[sd][sc], incl = wave_incl_sum(x);
+    if (tid % kWave == kWave - 1) s_w[w] = incl;
+    __syncthreads();
+    uint32_t before = 0;
+    for (int i = sd * NWd; i < w; ++i) before += s_w[i];
+    s_cs[sd][sc] = before + incl - x;
+    if (sc == kColChunks - 1 && blockIdx.x * kColDigits + sd < a.nd)
+      a.totals[blockIdx.x * kColDigits + sd] = before + incl;
   }
-  if (ok && c == 0) a.totals[d] = total;
+  __syncthreads();
+  uint32_t run = s_cs[dl][c];
+#pragma unroll 1
   for (int tb = t0; tb < t1; tb += kColBatch) {
-    uint32_t v[kColBatch];
-#pragma unroll
-    for (int i = 0; i < kColBatch; ++i) v[i] = ok && tb + i < t1 ? a.counts[(size_t)(tb + i) * a.stride + d] : 0u;
+    if (ct > kColBatch) load_batch(tb);
 #pragma unroll
     for (int i = 0; i < kColBatch; ++i) {
       if (ok && tb + i < t1) {
@@ -899,7 +934,7 @@ struct UniqArgs {
   int32_t* seg;
   int32_t* num_unique;
   int32_t* chunk_seg;  // [nchunks+1]: segment of position c*kChunk; [nchunks] = U
-  uint64_t* status;    // [tiles], zeroed by k_prepare of the same call
+  uint64_t* status;    // [tiles], zeroed by the first sort pass of the same call
   uint32_t* prev_totals;  // the last sort pass's totals, cleared here
   const uint64_t* prefix;  // reduce-then-scan: each tile's (heads, last head position + 1) over the
                            // tiles before it, from k_uniq_counts and k_uniq_scan; null: look-back
@@ -1008,6 +1043,7 @@ __global__ __launch_bounds__(kUniqScanThreads) void k_uniq_scan(uint64_t* words,
 __device__ __forceinline__ void unique_tile(const UniqArgs& a, const int tile) {
   constexpr int NW = kUniqThreads / kWave;
   __shared__ uint32_t s_keys[kUniqTile];
+  __shared__ uint16_t s_head[kUniqTile];
   __shared__ uint32_t s_wc[NW], s_wq[NW];
   __shared__ uint32_t s_pc, s_pq, s_prev, s_fail;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
@@ -1059,22 +1095,18 @@ __device__ __forceinline__ void unique_tile(const UniqArgs& a, const int tile) {
       }
     }
   }
-  // block exclusive scan of (count sum, last-head max)
+  // block exclusive scan of the heads' count; the tile's count and last head
   const uint32_t ci = wave_incl_sum(c);
   const uint32_t qi = wave_incl_max(q);
   if (lane == kWave - 1) {
     s_wc[w] = ci;
     s_wq[w] = qi;
   }
-  const uint32_t q_before_lane = __shfl_up(qi, 1, kWave);
   __syncthreads();
-  uint32_t c_ex = ci - c, q_ex = lane > 0 ? q_before_lane : 0u;
+  uint32_t c_ex = ci - c;
   uint32_t tile_c = 0, tile_q = 0;
   for (int ww = 0; ww < NW; ++ww) {
-    if (ww < w) {
-      c_ex += s_wc[ww];
-      q_ex = max(q_ex, s_wq[ww]);
-    }
+    if (ww < w) c_ex += s_wc[ww];
     tile_c += s_wc[ww];
     tile_q = max(tile_q, s_wq[ww]);
   }
@@ -1164,28 +1196,34 @@ __device__ __forceinline__ void unique_tile(const UniqArgs& a, const int tile) {
     if (last_tile && tid == 0) a.num_unique[0] = 0;
     return;
   }
-  uint32_t u = s_pc + c_ex;
-  uint32_t lastq = max(s_pq, q_ex);
+  // the tile's heads, packed in LDS, so that what is written of them is
+  // written in order (from where the positions lie, a store's lanes would be
+  // eight positions apart)
+  uint32_t hc = c_ex;
 #pragma unroll
-  for (int i = 0; i < kUniqItems; ++i) {
-    const int s = tid * kUniqItems + i;
-    const int64_t pos = tbase + s;
-    if (pos < a.N) {
-      if (heads & (1u << i)) {
-        a.ukeys[u] = s_keys[s] & a.key_mask;
-        a.seg[u] = (int32_t)pos;
-        if (u > 0) a.counts[u - 1] = (int32_t)pos - (int32_t)(lastq - 1u);
-        lastq = (uint32_t)pos + 1u;
-        ++u;
-      }
-      if (pos % kChunk == 0) a.chunk_seg[pos / kChunk] = (int32_t)u - 1;
-      if (pos == a.N - 1) {
-        a.num_unique[0] = (int32_t)u;
-        a.seg[u] = a.N;
-        a.counts[u - 1] = a.N - (int32_t)(lastq - 1u);
-        a.chunk_seg[a.nchunks] = (int32_t)u;
-      }
-    }
+  for (int i = 0; i < kUniqItems; ++i)
+    if (heads & (1u << i)) s_head[hc++] = (uint16_t)(tid * kUniqItems + i);
+  // segment of each chunk's first position
+  static_assert(kChunk % kUniqItems == 0, "a chunk starts at a thread's first position");
+  const int64_t first = tbase + tid * kUniqItems;
+  if (tid % (kChunk / kUniqItems) == 0 && first < a.N)
+    a.chunk_seg[first / kChunk] = (int32_t)(s_pc + c_ex + (heads & 1u)) - 1;
+  __syncthreads();
+  const uint32_t u0 = s_pc;
+  for (uint32_t i = tid; i < tile_c; i += kUniqThreads) {
+    const int32_t s = s_head[i], pos = (int32_t)tbase + s;
+    a.ukeys[u0 + i] = s_keys[s] & a.key_mask;
+    a.seg[u0 + i] = pos;
+    // the last head's segment ends in a later tile, whose first head writes its count
+    if (i + 1 < tile_c) a.counts[u0 + i] = (int32_t)s_head[i + 1] - s;
+    if (i == 0 && u0 > 0) a.counts[u0 - 1] = pos - (int32_t)(s_pq - 1u);
+  }
+  if (last_tile && tid == 0) {
+    const uint32_t U = u0 + tile_c;
+    a.num_unique[0] = (int32_t)U;
+    a.seg[U] = a.N;
+    a.counts[U - 1] = a.N - (int32_t)(max(s_pq, tile_q) - 1u);
+    a.chunk_seg[a.nchunks] = (int32_t)U;
   }
 }
 
@@ -1312,37 +1350,14 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
     rts_it = kSortItemsCore;
   const int tile_keys = kSortThreads * (sort_cores ? sort_it : rts_it);
   const int sort_tiles = (N + tile_keys - 1) / tile_keys;
-  // int32 ids of one table are the keys: the first pass then reads them and
-  // finds each position's bag itself, with no prepare kernel
-  const bool first_pass_bags = p.T == 1 && !p.idx64;
   const int uniq_cores =
       !p.waitfree && uniq_tiles <= resident_blocks(reinterpret_cast<const void*>(&k_unique), kUniqThreads);
-  uint32_t* keys_built = reinterpret_cast<uint32_t*>(ws + L.keys_built);
   hipError_t e = hipSuccess;
 
-  if (!sort_cores && !first_pass_bags) {
-    PrepArgs pa{};
-    pa.offsets = p.offsets;
-    pa.idx = p.idx;
-    pa.idx64 = p.idx64;
-    pa.ro = p.ro;
-    pa.B = p.B;
-    pa.M = p.M;
-    // about kPrepPositions positions per block
-    const int64_t want = (int64_t)kPrepPositions * p.M / N;
-    pa.bags_per_block = (int)(want < 1 ? 1 : (want > kPrepMaxBags ? kPrepMaxBags : want));
-    // int32 ids of one table are the keys themselves; otherwise keys are built
-    pa.keys_out = (p.T > 1 || p.idx64) ? keys_built : nullptr;
-    pa.bag_of = reinterpret_cast<int32_t*>(ws + L.bag_of);
-    const int prep_blocks = p.M > 0 ? (p.M + pa.bags_per_block - 1) / pa.bags_per_block : 1;
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)prep_blocks), dim3(kPrepThreads), 0, s, pa);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-
-  const uint32_t* kin = (p.T > 1 || p.idx64) ? keys_built : static_cast<const uint32_t*>(p.idx);
+  // the first pass reads the ids themselves and finds each position's bag
+  const uint32_t* kin = nullptr;
   const int32_t* vin = nullptr;
-  const int32_t* bin = reinterpret_cast<const int32_t*>(ws + L.bag_of);
+  const int32_t* bin = nullptr;
   uint32_t* keys_a = reinterpret_cast<uint32_t*>(ws + L.keys_a);
   uint32_t* keys_b = reinterpret_cast<uint32_t*>(ws + L.keys_b);
   int32_t* vals_a = reinterpret_cast<int32_t*>(ws + L.vals_a);
@@ -1373,7 +1388,7 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
       xa.pass_shift[i] = p.plan.shift[i];
       xa.pass_bits[i] = p.plan.bits[i];
     }
-    xa.search_bags = ps == 0 && (sort_cores || first_pass_bags);
+    xa.search_bags = ps == 0;
     xa.offsets = p.offsets;
     xa.idx = p.idx;
     xa.idx64 = p.idx64;
@@ -1381,6 +1396,7 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
     xa.B = p.B;
     xa.M = p.M;
     xa.T = p.T;
+    xa.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
     xa.uniq_status = reinterpret_cast<uint64_t*>(ws + L.uniq_status);
     xa.uniq_tiles = uniq_tiles;
     xa.hdr = hdr;
@@ -1401,6 +1417,14 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
       ca.bits = xa.bits;
       ca.stride = status_stride;
       ca.counts = counts;
+      if (ps == 0) {
+        ca.idx = p.idx;
+        ca.idx64 = p.idx64;
+        ca.B = p.B;
+        ca.T = p.T;
+        ca.offsets = p.offsets;
+        ca.ro = p.ro;
+      }
       if (rts_it == kSortItemsCore)
         hipLaunchKernelGGL(k_tile_counts<kSortItemsCore>, dim3((unsigned)sort_tiles), dim3(kSortThreads), 0, s, ca);
       else

@@ -38,8 +38,9 @@ constexpr int kPrefixGroup = 16;
 // block, and the most tiles one of its threads sums
 constexpr int kRangeDigits = 32;
 constexpr int kRangeTiles = 16;
-// bag offsets a first-pass tile stages in LDS to find the bag of each position
-constexpr int kBagStage = 2048;
+// most bags, in the sample intervals around a first-pass tile's, that the tile
+// reads one by one to find the bag of each position (above, it searches)
+constexpr int kBagMarks = 32768;
 
 // prepare kernel (keys, bag ids, digit histograms)
 constexpr int kPrepThreads = 256;
