@@ -128,8 +128,6 @@ struct PassArgs {
   const uint32_t* prefix;  // reduce-then-scan (tiles not co-resident): [tiles][status_stride], each digit's
                            // count in the tiles before this one, from k_tile_counts and k_column_scan
   int32_t xcd_order;       // 1: tiles in XCD order (xcd_tile), for passes of many tiles that read their offsets
-  int32_t coresident;      // 1: every tile is resident at once (tile = block index, prefix blocks
-                           //    after the tiles publish each tile's final digit offsets)
   int32_t prefix_mode;     // co-resident: kPrefixGroups or kPrefixRanges
   // first co-resident pass: the later passes' digit counts are published in
   // `later` [tiles][kMaxPasses - 1][status_stride] and summed into their
@@ -184,33 +182,33 @@ __device__ __forceinline__ void block_excl_scan(uint32_t* arr, uint32_t* s_wsum)
   __syncthreads();
 }
 
-// Two-level prefix of a co-resident pass, for digit d.  Published words are
-// (tag << 32 | count).  A batch of words is loaded together; the words that
-// do not carry this pass's tag yet are loaded again together after a short
-// sleep, so every retry round costs one memory round trip however many words
-// are stale.  The wait is bounded in time (kWaitTicks).
+// Published words of a co-resident pass, for digit d: (tag << 32 | count) of
+// tiles [lo, lo + n).  They are loaded together, and again together after a
+// short sleep until all carry this pass's tag, so every round costs one memory
+// round trip however many words are stale (words past n stand in as zeros).
+// The wait is bounded in time (kWaitTicks).  One loop, whose code is fetched
+// once: the passes are microseconds long, and what they unroll has to be
+// fetched as instructions first.
 template <int K>
 __device__ __forceinline__ void poll_batch(const uint64_t* base, int stride, int lo, int n, int d, uint64_t tag,
                                            WsHeader* h, uint32_t g, uint32_t site, uint64_t (&v)[K]) {
-  // words past n stand in as ready
-  uint32_t stale = 0;
-#pragma unroll
-  for (int i = 0; i < K; ++i) stale |= (i < n && !word_current(v[i], tag)) ? (1u << i) : 0u;
+  const uint64_t* p = base + (size_t)lo * stride + d;
   uint32_t spins = 0;
-  const uint64_t t0 = stale ? wait_clock() : 0;
-  while (stale) {
+  uint64_t t0 = 0;
+#pragma unroll 1
+  for (;;) {
+#pragma unroll
+    for (int i = 0; i < K; ++i) v[i] = i < n ? ld_relaxed_u64(p + (size_t)i * stride) : 0;
+    bool stale = false;
+#pragma unroll
+    for (int i = 0; i < K; ++i) stale |= i < n && !word_current(v[i], tag);
+    if (!stale) break;
+    if (spins == 0) t0 = wait_clock();
     if (wait_over(h, g, t0, ++spins)) {
       flag_timeout(h, g, site);
       break;
     }
     __builtin_amdgcn_s_sleep(1);
-    const uint64_t* p = base + (size_t)lo * stride + d;
-#pragma unroll
-    for (int i = 0; i < K; ++i)
-      if (stale & (1u << i)) v[i] = ld_relaxed_u64(p + (size_t)i * stride);
-    stale = 0;
-#pragma unroll
-    for (int i = 0; i < K; ++i) stale |= (i < n && !word_current(v[i], tag)) ? (1u << i) : 0u;
   }
 }
 
@@ -226,8 +224,6 @@ __device__ __forceinline__ void group_counts(const uint64_t* rows, uint64_t* grp
                                              uint32_t& last_pre) {
   uint64_t v[kPrefixGroup];
   const int n = g1 - g0;
-#pragma unroll
-  for (int i = 0; i < kPrefixGroup; ++i) v[i] = i < n ? ld_relaxed_u64(rows + (size_t)(g0 + i) * stride + d) : 0;
   poll_batch<kPrefixGroup>(rows, stride, g0, n, d, tag, h, gcall, site, v);
   uint32_t run = 0;
   last_pre = 0;
@@ -250,8 +246,6 @@ __device__ __forceinline__ void group_sums(const uint64_t* grp, int stride, int 
   for (int base = 0; base < ngroups; base += kPrefixGroup) {
     const int n = min(kPrefixGroup, ngroups - base);
     uint64_t gv[kPrefixGroup];
-#pragma unroll
-    for (int i = 0; i < kPrefixGroup; ++i) gv[i] = i < n ? ld_relaxed_u64(grp + (size_t)(base + i) * stride + d) : 0;
     poll_batch<kPrefixGroup>(grp, stride, base, n, d, tag, h, gcall, site, gv);
 #pragma unroll
     for (int i = 0; i < kPrefixGroup; ++i) {
@@ -330,8 +324,6 @@ __device__ __forceinline__ void sort_prefix_block(const PassArgs& a, uint32_t gc
         if (d < (1 << a.pass_bits[p])) {
           const uint64_t* lb = a.later + (size_t)(p - 1) * a.status_stride;
           uint64_t v[kPrefixGroup];
-#pragma unroll
-          for (int i = 0; i < kPrefixGroup; ++i) v[i] = i < n ? ld_relaxed_u64(lb + (size_t)(g0 + i) * lstride + d) : 0;
           poll_batch<kPrefixGroup>(lb, (int)lstride, g0, n, d, tag, a.hdr, gcall,
                                    kSiteLaterCounts | ((uint32_t)a.pass << 4), v);
           uint32_t sum = 0;
@@ -372,9 +364,6 @@ __device__ __forceinline__ void sort_prefix_range(const PassArgs& a, uint32_t gc
   block_excl_scan<RB>(s_base, s_wsum);
   // this digit's counts in the chunk's tiles
   uint64_t v[kRangeTiles];
-#pragma unroll
-  for (int i = 0; i < kRangeTiles; ++i)
-    v[i] = i < n ? ld_relaxed_u64(a.rows + (size_t)(t0 + i) * a.status_stride + d) : 0;
   poll_batch<kRangeTiles>(a.rows, a.status_stride, t0, n, d, tag, a.hdr, gcall,
                           kSiteRangeCounts | ((uint32_t)a.pass << 4), v);
   uint32_t sum = 0;
@@ -525,7 +514,10 @@ struct PassLds {
   static_assert(TILE < 65536, "per-wave counters fit 16 bits");
 };
 
-template <int RB, int IT>
+// CORE: every tile is resident at once (tile = block index, prefix blocks after
+// the tiles publish each tile's final digit offsets); otherwise the offsets
+// were computed before the pass.
+template <int RB, int IT, bool CORE>
 __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   using Lds = PassLds<RB, IT>;
   constexpr int ND = Lds::ND;
@@ -547,7 +539,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
   // co-resident: the histograms start from zero (the per-wave counters are
   // cleared after them); otherwise the per-wave counters at once
-  if (a.coresident)
+  if (CORE)
     for (int i = tid; i < kMaxPasses * ND; i += kSortThreads) s_hist[i] = 0u;
   else
     for (int i = tid; i < NW * ND / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(s_arena + Lds::kCnt)[i] = 0u;
@@ -557,14 +549,14 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   if (blockIdx.x == 0 && a.prev_totals)
     for (int d = tid; d < kMaxDigits; d += kSortThreads) a.prev_totals[d] = 0u;
   __syncthreads();
-  const int tile = a.xcd_order && (int)blockIdx.x < a.ntiles ? xcd_tile((int)blockIdx.x, a.ntiles) : (int)blockIdx.x;
+  const int tile = !CORE && a.xcd_order ? xcd_tile((int)blockIdx.x, a.ntiles) : (int)blockIdx.x;
   const uint32_t mask = (1u << a.bits) - 1u;
   // the call's generation (the header's advances once per call, in the
   // unique scan) and this pass's tag
   const uint32_t gcall = next_gen(a.hdr->gen);
   const uint64_t tag = word_tag(gcall, (uint32_t)a.pass);
   if (a.pass == 0 && blockIdx.x == 0 && tid == 0) a.hdr->cur = gcall;
-  if (a.coresident && (int)blockIdx.x >= a.ntiles) {
+  if (CORE && (int)blockIdx.x >= a.ntiles) {
     uint32_t* s_pre = reinterpret_cast<uint32_t*>(s_arena);
     uint32_t* s_base = s_pre + (kPrefixGroup / 2) * ND;
     if (a.prefix_mode == kPrefixRanges) sort_prefix_range<RB>(a, gcall, tag, s_pre, s_wsum, s_pre + ND);
@@ -584,7 +576,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   // (from an LDS histogram), so that the other tiles' prefixes advance while
   // this tile finds its bags, ranks and reorders its keys.
   auto publish_counts = [&]() {
-    if (!a.coresident) return;  // the offsets were computed before the pass
+    if (!CORE) return;  // the offsets were computed before the pass
 #pragma unroll
     for (int i = 0; i < IT; ++i) hist_add(s_hist, dig[i], wbase + i * kWave + lane < a.N, lane);
     if (a.later) {
@@ -655,7 +647,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
     publish_counts();
   }
   // the histograms are out: the per-wave counters start from zero
-  if (a.coresident) {
+  if (CORE) {
     __syncthreads();
     for (int i = tid; i < NW * ND / 2; i += kSortThreads) reinterpret_cast<uint32_t*>(s_arena + Lds::kCnt)[i] = 0u;
     __syncthreads();
@@ -693,14 +685,14 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
         run += c;
       }
       s_tstart[d] = run;
-      if (!a.coresident) s_gbase[d] = a.totals[d];
+      if (!CORE) s_gbase[d] = a.totals[d];
     }
   }
 
   uint32_t excl[DPT];
   __syncthreads();
   block_excl_scan<RB>(s_tstart, s_wsum);
-  if (!a.coresident) block_excl_scan<RB>(s_gbase, s_wsum);
+  if (!CORE) block_excl_scan<RB>(s_gbase, s_wsum);
 
   // reorder the tile in LDS by digit (stable); only tile-local offsets are
   // needed, so this is done before the wait for the other tiles' counts.
@@ -716,7 +708,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
     }
   }
 
-  if (a.coresident) {
+  if (CORE) {
     // the final offset of every digit arrives from this tile's group's
     // prefix block; only this tile's words are polled
 #pragma unroll
@@ -724,7 +716,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
       const int d = tid + k * kSortThreads;
       excl[k] = 0;
       if (d < ND) {
-        uint64_t fv[1] = {ld_relaxed_u64(a.status + (size_t)tile * a.status_stride + d)};
+        uint64_t fv[1];
         poll_batch<1>(a.status, a.status_stride, tile, 1, d, tag, a.hdr, gcall,
                       kSiteTileOffsets | ((uint32_t)a.pass << 4), fv);
         excl[k] = word_count(fv[0]);
@@ -756,6 +748,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   const int64_t tstart = (int64_t)tile * TILE;
   const int nvalid = (int)min((int64_t)TILE, (int64_t)a.N - tstart);
   uint32_t dst[IT];
+  bool bad = false;  // digit totals inconsistent with the keys, or a key outside its member's share
 #pragma unroll
   for (int j = 0; j < IT; ++j) {
     const int s = tid + j * kSortThreads;
@@ -766,19 +759,20 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
       dst[j] = s_gbase[d] + (uint32_t)s - s_tstart[d];
       if (dst[j] < (uint32_t)a.N) {
         a.keys_out[dst[j]] = k;
-        if (a.split_n > 0) {
+        if (!CORE && a.split_n > 0) {
           const uint32_t m = a.split_n > 1 ? k >> a.split_bits : 0u;
           const uint32_t o = dst[j] - (uint32_t)a.split_P[m < (uint32_t)a.split_n ? m : 0];
           if (m < (uint32_t)a.split_n && o < (uint32_t)a.split_N[m]) a.split_perm[m][o] = s_vals[s] - a.split_P[m];
-          else flag_error(a.hdr, gcall, 2u);  // a key outside its member's share
+          else bad = true;
         } else {
           a.vals_out[dst[j]] = s_vals[s];
         }
       } else {
-        flag_error(a.hdr, gcall, 2u);  // digit totals inconsistent with the keys
+        bad = true;
       }
     }
   }
+  if (bad) flag_error(a.hdr, gcall, 2u);
   __syncthreads();
 #pragma unroll
   for (int i = 0; i < IT; ++i)
@@ -788,7 +782,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   for (int j = 0; j < IT; ++j) {
     if (dst[j] >= (uint32_t)a.N) continue;
     const int s = tid + j * kSortThreads;
-    if (a.split_n > 0) {
+    if (!CORE && a.split_n > 0) {
       const uint32_t m = a.split_n > 1 ? s_keys[s] >> a.split_bits : 0u;
       if (m < (uint32_t)a.split_n) {
         const uint32_t o = dst[j] - (uint32_t)a.split_P[m];
@@ -1236,41 +1230,41 @@ __global__ void k_unique_empty(int32_t* num_unique, int32_t* seg) {
   }
 }
 
-template <int RB, int IT>
+template <int RB, int IT, bool CORE>
 hipError_t launch_pass(const PassArgs& pa, int tiles, hipStream_t s) {
-  hipLaunchKernelGGL((k_sort_pass<RB, IT>), dim3((unsigned)tiles), dim3(kSortThreads), 0, s, pa);
+  hipLaunchKernelGGL((k_sort_pass<RB, IT, CORE>), dim3((unsigned)tiles), dim3(kSortThreads), 0, s, pa);
   return hipGetLastError();
 }
 
 template <int IT>
 const void* pass_kernel_bits(int bits) {
   switch (bits) {
-    case 1: return reinterpret_cast<const void*>(&k_sort_pass<1, IT>);
-    case 2: return reinterpret_cast<const void*>(&k_sort_pass<2, IT>);
-    case 3: return reinterpret_cast<const void*>(&k_sort_pass<3, IT>);
-    case 4: return reinterpret_cast<const void*>(&k_sort_pass<4, IT>);
-    case 5: return reinterpret_cast<const void*>(&k_sort_pass<5, IT>);
-    case 6: return reinterpret_cast<const void*>(&k_sort_pass<6, IT>);
-    case 7: return reinterpret_cast<const void*>(&k_sort_pass<7, IT>);
-    case 8: return reinterpret_cast<const void*>(&k_sort_pass<8, IT>);
-    case 9: return reinterpret_cast<const void*>(&k_sort_pass<9, IT>);
-    default: return reinterpret_cast<const void*>(&k_sort_pass<10, IT>);
+    case 1: return reinterpret_cast<const void*>(&k_sort_pass<1, IT, true>);
+    case 2: return reinterpret_cast<const void*>(&k_sort_pass<2, IT, true>);
+    case 3: return reinterpret_cast<const void*>(&k_sort_pass<3, IT, true>);
+    case 4: return reinterpret_cast<const void*>(&k_sort_pass<4, IT, true>);
+    case 5: return reinterpret_cast<const void*>(&k_sort_pass<5, IT, true>);
+    case 6: return reinterpret_cast<const void*>(&k_sort_pass<6, IT, true>);
+    case 7: return reinterpret_cast<const void*>(&k_sort_pass<7, IT, true>);
+    case 8: return reinterpret_cast<const void*>(&k_sort_pass<8, IT, true>);
+    case 9: return reinterpret_cast<const void*>(&k_sort_pass<9, IT, true>);
+    default: return reinterpret_cast<const void*>(&k_sort_pass<10, IT, true>);
   }
 }
 
-template <int IT>
+template <int IT, bool CORE>
 hipError_t launch_pass_bits(const PassArgs& pa, int tiles, hipStream_t s) {
   switch (pa.bits) {
-    case 1: return launch_pass<1, IT>(pa, tiles, s);
-    case 2: return launch_pass<2, IT>(pa, tiles, s);
-    case 3: return launch_pass<3, IT>(pa, tiles, s);
-    case 4: return launch_pass<4, IT>(pa, tiles, s);
-    case 5: return launch_pass<5, IT>(pa, tiles, s);
-    case 6: return launch_pass<6, IT>(pa, tiles, s);
-    case 7: return launch_pass<7, IT>(pa, tiles, s);
-    case 8: return launch_pass<8, IT>(pa, tiles, s);
-    case 9: return launch_pass<9, IT>(pa, tiles, s);
-    case 10: return launch_pass<10, IT>(pa, tiles, s);
+    case 1: return launch_pass<1, IT, CORE>(pa, tiles, s);
+    case 2: return launch_pass<2, IT, CORE>(pa, tiles, s);
+    case 3: return launch_pass<3, IT, CORE>(pa, tiles, s);
+    case 4: return launch_pass<4, IT, CORE>(pa, tiles, s);
+    case 5: return launch_pass<5, IT, CORE>(pa, tiles, s);
+    case 6: return launch_pass<6, IT, CORE>(pa, tiles, s);
+    case 7: return launch_pass<7, IT, CORE>(pa, tiles, s);
+    case 8: return launch_pass<8, IT, CORE>(pa, tiles, s);
+    case 9: return launch_pass<9, IT, CORE>(pa, tiles, s);
+    case 10: return launch_pass<10, IT, CORE>(pa, tiles, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1378,7 +1372,6 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
     xa.status = reinterpret_cast<uint64_t*>(back + L.pass_status);
     xa.rows = reinterpret_cast<uint64_t*>(back + L.rows);
     xa.grp = reinterpret_cast<uint64_t*>(back + L.grp);
-    xa.coresident = sort_cores;
     xa.xcd_order = !sort_cores && sort_tiles > kXcdOrderMinTiles;
     xa.prefix_mode = (sort_cores && ranges && ps > 0) ? kPrefixRanges : kPrefixGroups;
     xa.later = (sort_cores && ranges && ps == 0) ? reinterpret_cast<uint64_t*>(back + L.later) : nullptr;
@@ -1442,10 +1435,15 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
       xa.prefix = counts;
     }
     const int extra = sort_cores ? prefix_blocks(ps) : 0;
-    switch (sort_cores ? sort_it : rts_it) {
-      case kSortItemsCore: e = launch_pass_bits<kSortItemsCore>(xa, sort_tiles + extra, s); break;
-      case kSortItemsMid: e = launch_pass_bits<kSortItemsMid>(xa, sort_tiles + extra, s); break;
-      default: e = launch_pass_bits<kSortItemsWide>(xa, sort_tiles + extra, s);
+    if (sort_cores) {
+      switch (sort_it) {
+        case kSortItemsCore: e = launch_pass_bits<kSortItemsCore, true>(xa, sort_tiles + extra, s); break;
+        case kSortItemsMid: e = launch_pass_bits<kSortItemsMid, true>(xa, sort_tiles + extra, s); break;
+        default: e = launch_pass_bits<kSortItemsWide, true>(xa, sort_tiles + extra, s);
+      }
+    } else {
+      e = rts_it == kSortItemsCore ? launch_pass_bits<kSortItemsCore, false>(xa, sort_tiles, s)
+                                   : launch_pass_bits<kSortItemsWide, false>(xa, sort_tiles, s);
     }
     if (e != hipSuccess) return e;
     kin = xa.keys_out;
@@ -1689,7 +1687,6 @@ hipError_t launch_dedup_group(const GroupDedupLaunch& p, hipStream_t s) {
       xa.status = reinterpret_cast<uint64_t*>(back + L.pass_status);
       xa.rows = reinterpret_cast<uint64_t*>(back + L.rows);
       xa.grp = reinterpret_cast<uint64_t*>(back + L.grp);
-      xa.coresident = 0;
       xa.xcd_order = sort_tiles > kXcdOrderMinTiles;
       xa.prefix_mode = kPrefixGroups;
       xa.later = nullptr;
@@ -1743,8 +1740,8 @@ hipError_t launch_dedup_group(const GroupDedupLaunch& p, hipStream_t s) {
                          dim3(kColDigits * kColChunks), 0, s, sa);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       xa.prefix = counts;
-      e = it == kSortItemsCore ? launch_pass_bits<kSortItemsCore>(xa, sort_tiles, s)
-                               : launch_pass_bits<kSortItemsWide>(xa, sort_tiles, s);
+      e = it == kSortItemsCore ? launch_pass_bits<kSortItemsCore, false>(xa, sort_tiles, s)
+                               : launch_pass_bits<kSortItemsWide, false>(xa, sort_tiles, s);
       if (e != hipSuccess) return e;
       kin = xa.keys_out;
       vin = xa.vals_out;
