@@ -54,6 +54,7 @@ struct RouteArgs {
   TableOffsets ro;
   ShardBounds sb;
   int32_t B, M, W, owner_bits, bags_per_block, nblocks;
+  uint32_t b_magic;  // floor(2^32 / B) (B > 1)
   int32_t N;
   int32_t* counts;  // [W][nblocks]: a block's count of each owner, then its base within the owner's range
   int32_t* send_counts;
@@ -96,6 +97,18 @@ __device__ __forceinline__ int owner_of(const uint32_t* s_sb, int W, uint32_t ke
   return lo;
 }
 
+// positions a wavefront loads ids for before it routes the first of them
+constexpr int kRouteBatch = 4;
+
+// first global row of a bag's table (one table: no lookup; otherwise the
+// division by B as a multiplication, one too few at most)
+__device__ __forceinline__ uint32_t table_row(const RouteArgs& a, int bag) {
+  if (a.M <= a.B) return a.ro.off[0];
+  uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag, a.b_magic) : (uint32_t)bag;
+  if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag) ++t;
+  return a.ro.off[t];
+}
+
 __global__ __launch_bounds__(kWave) void k_route_count(RouteArgs a) {
   __shared__ int32_t s_off[kRouteBags + 1];
   __shared__ uint32_t s_sb[kMaxRanks + 1];
@@ -106,10 +119,15 @@ __global__ __launch_bounds__(kWave) void k_route_count(RouteArgs a) {
   stage(a, s_off, s_sb, b0, b1);
   const int nb = b1 - b0;
   const int32_t p0 = s_off[0], p1 = s_off[nb];
-  for (int32_t j = p0 + lane; j < p1; j += kWave) {
-    const int bl = bag_of(s_off, nb, j);
-    const uint32_t key = a.ro.off[(b0 + bl) / a.B] + (uint32_t)load_id(a.idx, a.idx64, j);
-    atomicAdd(&s_hist[owner_of(s_sb, a.W, key)], 1);
+  for (int32_t jb = p0 + lane; jb < p1; jb += kRouteBatch * kWave) {
+    uint32_t id[kRouteBatch];
+#pragma unroll
+    for (int u = 0; u < kRouteBatch; ++u) id[u] = jb + u * kWave < p1 ? (uint32_t)load_id(a.idx, a.idx64, jb + u * kWave) : 0u;
+#pragma unroll
+    for (int u = 0; u < kRouteBatch; ++u) {
+      const int32_t j = jb + u * kWave;
+      if (j < p1) atomicAdd(&s_hist[owner_of(s_sb, a.W, table_row(a, b0 + bag_of(s_off, nb, j)) + id[u])], 1);
+    }
   }
   __syncthreads();
   for (int r = lane; r < a.W; r += kWave) a.counts[(size_t)r * a.nblocks + blockIdx.x] = s_hist[r];
@@ -158,33 +176,41 @@ __global__ __launch_bounds__(kWave) void k_route_scatter(RouteArgs a) {
   stage(a, s_off, s_sb, b0, b1);
   const int nb = b1 - b0;
   const int32_t p0 = s_off[0], p1 = s_off[nb];
-  for (int32_t jb = p0; jb < p1; jb += kWave) {
-    const int32_t j = jb + lane;
-    const bool valid = j < p1;
-    int bl = 0, o = 0;
-    uint32_t key = 0;
-    if (valid) {
-      bl = bag_of(s_off, nb, j);
-      key = a.ro.off[(b0 + bl) / a.B] + (uint32_t)load_id(a.idx, a.idx64, j);
-      o = owner_of(s_sb, a.W, key);
+  for (int32_t jg = p0; jg < p1; jg += kRouteBatch * kWave) {
+    uint32_t id[kRouteBatch];
+#pragma unroll
+    for (int u = 0; u < kRouteBatch; ++u) {
+      const int32_t j = jg + u * kWave + lane;
+      id[u] = j < p1 ? (uint32_t)load_id(a.idx, a.idx64, j) : 0u;
     }
-    // lanes with the same owner, by one ballot per owner bit
-    uint64_t peers = __ballot(valid);
-    for (int bit = 0; bit < a.owner_bits; ++bit) {
-      const bool x = (o >> bit) & 1;
-      const uint64_t bx = __ballot(x);
-      peers &= x ? bx : ~bx;
+#pragma unroll
+    for (int u = 0; u < kRouteBatch; ++u) {
+      if (jg + u * kWave >= p1) break;
+      const int32_t j = jg + u * kWave + lane;
+      const bool valid = j < p1;
+      int bl = 0, o = 0;
+      uint32_t key = 0;
+      if (valid) {
+        bl = bag_of(s_off, nb, j);
+        key = table_row(a, b0 + bl) + id[u];
+        o = owner_of(s_sb, a.W, key);
+      }
+      // lanes with the same owner, by one ballot per owner bit
+      const uint64_t all = __ballot(valid);
+      uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+      for (int bit = 0; bit < a.owner_bits; ++bit) keep_peers((uint32_t)o, bit, lo, hi);
+      const uint64_t peers = ((uint64_t)hi << 32) | lo;
+      const int32_t dst = valid ? s_run[o] + (int32_t)lanes_below(peers) : 0;
+      if (valid && (uint32_t)dst < (uint32_t)a.N) {  // always, for well-formed offsets
+        a.send_ids[dst] = (int32_t)(key - s_sb[o]);
+        a.send_pos[dst] = j;
+        a.send_bag[dst] = b0 + bl;
+      }
+      __builtin_amdgcn_wave_barrier();
+      // the lowest lane of each owner advances that owner's position
+      if (valid && lanes_below(peers) == 0) s_run[o] += __popcll(peers);
+      __builtin_amdgcn_wave_barrier();
     }
-    const int32_t dst = valid ? s_run[o] + (int32_t)lanes_below(peers) : 0;
-    if (valid && (uint32_t)dst < (uint32_t)a.N) {  // always, for well-formed offsets
-      a.send_ids[dst] = (int32_t)(key - s_sb[o]);
-      a.send_pos[dst] = j;
-      a.send_bag[dst] = b0 + bl;
-    }
-    __builtin_amdgcn_wave_barrier();
-    // the lowest lane of each owner advances that owner's position
-    if (valid && lanes_below(peers) == 0) s_run[o] += __popcll(peers);
-    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -226,6 +252,7 @@ hipError_t launch_route(const RouteLaunch& p, hipStream_t s) {
   a.N = (int32_t)p.N;
   a.owner_bits = 0;
   while ((1 << a.owner_bits) < p.W) ++a.owner_bits;
+  a.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
   a.bags_per_block = plan.bags_per_block;
   a.nblocks = plan.nblocks;
   a.counts = static_cast<int32_t*>(p.ws);
