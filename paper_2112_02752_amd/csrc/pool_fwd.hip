@@ -13,6 +13,12 @@
 // row is a cache hit, and finding the repeats cost more instructions than
 // their loads.
 //
+// The rows of a round are added pairwise, as many additions as one after
+// another, and the rounds in double: one fp32 chain per lane group grows with
+// the bag, and adding the same row over and over rounds the same way each time
+// (one id 4096 times in a bag, rows of 256 fp32 values: 3e-5 off in the chain,
+// exact now; 4096 Zipf(1.2) ids, 64 values: 1.9e-6 and 4e-8).
+//
 // What bounds it: the rows the L2s miss, once the instructions per row are few
 // enough.  Merging repeats by hash classes, LDS shuffles and a select per
 // element, the kernel issued 640 vector instructions per bag of the 26-table
@@ -35,30 +41,30 @@ namespace emb {
 namespace {
 
 template <typename TW>
-struct Vec;  // 16 bytes of table row, added to fp32 accumulators
+struct Vec;  // 16 bytes of table row
 
 // (loaded raw, widened where it is used, so that every load of a round is
 // issued before the first one is waited for)
 template <>
 struct Vec<float> {
   static constexpr int kElems = 4;
-  __device__ __forceinline__ static void add(const uint4& v, float (&o)[4]) {
-    o[0] += __uint_as_float(v.x);
-    o[1] += __uint_as_float(v.y);
-    o[2] += __uint_as_float(v.z);
-    o[3] += __uint_as_float(v.w);
+  __device__ __forceinline__ static void widen(const uint4& v, float (&o)[4]) {
+    o[0] = __uint_as_float(v.x);
+    o[1] = __uint_as_float(v.y);
+    o[2] = __uint_as_float(v.z);
+    o[3] = __uint_as_float(v.w);
   }
 };
 
 template <>
 struct Vec<uint16_t> {
   static constexpr int kElems = 8;
-  __device__ __forceinline__ static void add(const uint4& v, float (&o)[8]) {
+  __device__ __forceinline__ static void widen(const uint4& v, float (&o)[8]) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      o[2 * i] += __uint_as_float(w[i] << 16);
-      o[2 * i + 1] += __uint_as_float(w[i] & 0xffff0000u);
+      o[2 * i] = __uint_as_float(w[i] << 16);
+      o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
     }
   }
 };
@@ -158,24 +164,41 @@ __device__ __forceinline__ void load_slots(const char* const (&col)[NV], uint32_
     load_slots<TW, G, NV, UN, FULL, U0, U + 1>(col, rowbytes, row, u0, cnt, g, raw);
   }
 }
-template <typename TW, int G, int NV, int UN, bool FULL, int U0>
+// vector v of rows [U, U + N) of a round (N a power of two), added pairwise
+template <typename TW, int U, int N, int UN, int NV>
+__device__ __forceinline__ void sum_round(const uint4 (&raw)[UN][NV], int v, float (&o)[Vec<TW>::kElems]) {
+  if constexpr (N == 1) {
+    Vec<TW>::widen(raw[U][v], o);
+  } else {
+    float x[Vec<TW>::kElems];
+    sum_round<TW, U, N / 2>(raw, v, o);
+    sum_round<TW, U + N / 2, N / 2>(raw, v, x);
+#pragma unroll
+    for (int e = 0; e < Vec<TW>::kElems; ++e) o[e] += x[e];
+  }
+}
+// (A: float where a bag is one round, else double)
+template <typename TW, int G, int NV, int UN, bool FULL, int U0, typename A>
 __device__ __forceinline__ void add_slots(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
-                                          int cnt, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+                                          int cnt, int g, A (&acc)[NV][Vec<TW>::kElems]) {
   uint4 raw[UN][NV];
   load_slots<TW, G, NV, UN, FULL, U0>(col, rowbytes, row, u0, cnt, g, raw);
 #pragma unroll
-  for (int u = 0; u < UN; ++u)
+  for (int v = 0; v < NV; ++v) {
+    float t[Vec<TW>::kElems];
+    sum_round<TW, 0, UN>(raw, v, t);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Vec<TW>::add(raw[u][v], acc[v]);
+    for (int e = 0; e < Vec<TW>::kElems; ++e) acc[v][e] += (A)t[e];
+  }
 }
 
 // The slots of a chunk of ids from u0 on, nall of them present in every group
 // and nmax in some group (both uniform): whole rounds without masks, then one
 // masked round just long enough for what is left (a short bag does not pay
 // for a long round).
-template <typename TW, int G, int NV, int UN, int U0>
+template <typename TW, int G, int NV, int UN, int U0, typename A>
 __device__ __forceinline__ void add_rest(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
-                                         int cnt, int nmax, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+                                         int cnt, int nmax, int g, A (&acc)[NV][Vec<TW>::kElems]) {
   if constexpr (UN > 1) {
     if (nmax - u0 <= UN / 2) {
       add_rest<TW, G, NV, UN / 2, U0>(col, rowbytes, row, u0, cnt, nmax, g, acc);
@@ -184,9 +207,9 @@ __device__ __forceinline__ void add_rest(const char* const (&col)[NV], uint32_t 
   }
   add_slots<TW, G, NV, UN, false, U0>(col, rowbytes, row, u0, cnt, g, acc);
 }
-template <typename TW, int G, int NV, int U0 = 0>
+template <typename TW, int G, int NV, int U0 = 0, typename A>
 __device__ __forceinline__ void add_chunk(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int cnt,
-                                          int nall, int nmax, int g, float (&acc)[NV][Vec<TW>::kElems]) {
+                                          int nall, int nmax, int g, A (&acc)[NV][Vec<TW>::kElems]) {
   constexpr int UN = slots_in_flight(G, NV);
   if constexpr (G >= 32) {
     int u0 = 0;
@@ -213,14 +236,11 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
   const TI* idx = static_cast<const TI*>(a.idx);
   const uint32_t rowbytes = (uint32_t)a.D * (uint32_t)sizeof(TW);
 
-  float acc[NV][E];
   const char* col[NV];  // this lane's columns (lanes past the row's end stand in at column 0, stored by none)
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     const int c0 = (v * G + sub) * E;
     col[v] = static_cast<const char*>(a.W) + (size_t)(c0 < a.D ? c0 : 0) * sizeof(TW);
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[v][e] = 0.f;
   }
 
   // table of a bag: the division by B as a multiplication, one too few at most
@@ -258,6 +278,8 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
         // P bags lie in at most two tables
         const uint32_t base = m0 + g < (t + 1) * a.B ? a.ro.off[t] : a.ro.off[t + 1];
         const uint32_t row = sub < len ? base + (uint32_t)(int32_t)idx[start + sub] : 0u;
+        static_assert(kShortBag <= 8 && NV == 1, "a short bag is one round");
+        float acc[NV][E] = {};
         add_chunk<TW, G, NV>(col, rowbytes, row, len, R > P ? 0 : lmin, lmax, g, acc);
         const float scale = (a.pool == EMB_POOL_MEAN && len > 0) ? 1.0f / (float)len : 1.0f;
         float* op = a.out + (size_t)(m0 + g) * (size_t)a.D;
@@ -289,12 +311,18 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
   // one bag: group g takes ids g, g + R, g + 2R, ... of every 64
   const int start = __builtin_amdgcn_readfirstlane(first), end = __builtin_amdgcn_readfirstlane(last);
   const uint32_t base = a.ro.off[table_of(m)];
+  double sum[NV][E] = {};
   for (int j0 = start; j0 < end; j0 += kWave) {
     const int n = min(kWave, end - j0);
     const int k = sub * R + g;
     const uint32_t row = k < n ? base + (uint32_t)(int32_t)idx[j0 + k] : 0u;
-    add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, acc);
+    add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, sum);
   }
+  float acc[NV][E];
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[v][e] = (float)sum[v][e];
   sum_groups<G>(acc);
 
   const int L = end - start;

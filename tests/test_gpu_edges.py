@@ -65,6 +65,44 @@ def test_forward_short_and_long_bags(dtype, D, B):
         parity.run_case(ro, W, off, idx, G, B, "sum", "sgd", 0.5, 0.0, exact=dtype == "fp32", idx64=idx64)
 
 
+# rows held by 1, 2, 4 and 16 lane groups of a wavefront, and rows of several vectors per lane
+@pytest.mark.parametrize("dtype,D", [("fp32", 16), ("fp32", 64), ("fp32", 128), ("fp32", 256), ("fp32", 1024),
+                                     ("bf16", 128), ("bf16", 512)])
+@pytest.mark.parametrize("ids", ["one id", "skewed", "any"])
+def test_forward_precision_of_long_bags(dtype, D, ids):
+    """Bags of up to 20000 ids, of one id over and over, mostly of a few hot
+    ids, or of any: with rows of one sign, an element's relative error is at
+    most one fp32 rounding for each of the pairwise additions of a round of
+    rows (3) and of the lane groups (6), one for the double sum's conversion
+    and two for the mean's scale, 2^-24 each, however long the bag."""
+    import torch
+    import paper_2112_02752_amd as emb
+    print(f"case forward precision {dtype} D={D} {ids}", flush=True)
+    rng = np.random.default_rng(D)
+    R = 3000
+    lens = np.array([1, 7, 30, 64, 65, 200, 1000, 4096, 20000])
+    off = _offsets(lens)
+    if ids == "one id":
+        idx = np.repeat(rng.integers(0, R, size=len(lens)), lens)
+    elif ids == "skewed":
+        idx = (rng.zipf(1.5, size=off[-1]) - 1) % R
+    else:
+        idx = rng.integers(0, R, size=off[-1])
+    W = torch.from_numpy(rng.uniform(0.5, 1.5, size=(R, D)).astype(np.float32))
+    W = W if dtype == "fp32" else W.to(torch.bfloat16)
+    t = emb.Tables(W.cuda(), [0, R])
+    rows = W.double().numpy()
+    for pool in ("sum", "mean"):
+        b = emb.Batch(torch.from_numpy(off).cuda(), torch.from_numpy(idx.astype(np.int32)).cuda(), len(lens))
+        out = torch.zeros((len(lens), D), device="cuda")
+        emb.pool_fwd(t, b, pool, out)
+        for m, L in enumerate(lens):
+            n = np.bincount(idx[off[m]:off[m + 1]], minlength=R).astype(np.float64)
+            ref = (n @ rows) / (L if pool == "mean" else 1)
+            err = np.abs(out[m].cpu().numpy().astype(np.float64) - ref) / ref
+            assert err.max() <= 12 * 2.0 ** -24, (L, pool, err.max())
+
+
 def _segments_case(rng, seg_lens, M, repeat):
     """A one-table batch of M bags whose sorted keys have the given segment
     lengths; `repeat` positions of a bag carry the same id in a row."""
