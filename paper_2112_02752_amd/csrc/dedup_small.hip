@@ -108,7 +108,8 @@ __global__ __launch_bounds__(kThreads) void k_dedup_small(SmallArgs a) {
   for (int ps = 0; ps < a.passes; ++ps) {
     const int shift = a.shift[ps], bits = a.bits[ps], nd = 1 << bits;
     const uint32_t mask = (uint32_t)nd - 1u;
-    for (int i = lane; i < nd / 2; i += kWave) reinterpret_cast<uint32_t*>(s_cnt[w])[i] = 0u;
+    for (int i = lane; i < nd / 2; i += kWave) reinterpret_cast<lds_word*>(s_cnt[w])[i] = 0u;
+    wave_lds_order();
     uint32_t rank[IT];
     // rank of each key among its wavefront's earlier keys of its digit
     uint32_t lo[IT], hi[IT];
@@ -134,6 +135,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup_small(SmallArgs a) {
         rank[i] = c + r;
         if (r == 0) s_cnt[w][d] = (uint16_t)(c + (uint32_t)__popcll(peers));
       }
+      wave_lds_order();
     }
     __syncthreads();
     // per digit the wavefronts' offsets, then the digits' starts

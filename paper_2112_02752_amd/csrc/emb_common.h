@@ -230,6 +230,17 @@ __device__ __forceinline__ void keep_peers(uint32_t d, int b, uint32_t& lo, uint
   hi &= ~((uint32_t)(bb >> 32) ^ (uint32_t)m);
 }
 
+// Between LDS accesses of different lanes of one wavefront: what a lane wrote
+// before it, the others read after it.  No instruction (a wavefront's LDS
+// accesses are carried out in program order), but the compiler moves none of
+// them across.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+// a word over narrower LDS elements (may alias them, as the elements' own type may not)
+typedef uint32_t __attribute__((may_alias)) lds_word;
+
 // device-coherent (agent scope) loads and stores of words other workgroups
 // publish or poll; relaxed: a poll re-reads until the word carries its tag
 __device__ __forceinline__ uint64_t ld_relaxed_u64(const uint64_t* p) {
