@@ -26,6 +26,7 @@ import argparse
 import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -39,9 +40,25 @@ HBM_PEAK_GBS = 8000.0
 METRIC = "pooled lookups/sec (fwd+bwd+update) and achieved HBM GB/s vs peak, 1 GPU"
 COUNTERS = os.path.join(ROOT, "profiles", "c3_step_hbm_counters.txt")
 _CSRC = os.path.join(ROOT, "paper_2112_02752_amd", "csrc")
-PHASE_SOURCES = {"fwd": [os.path.join(_CSRC, "pool_fwd.hip")],
-                 "dedup": [os.path.join(_CSRC, "dedup.hip"), os.path.join(_CSRC, "emb_common.h")],
-                 "bwd_update": [os.path.join(_CSRC, "reduce.hip"), os.path.join(_CSRC, "emb_common.h")]}
+
+
+def _with_headers(*names):
+    """The sources and every header of their folder that they include, directly or not."""
+    files, todo = [], [os.path.join(_CSRC, n) for n in names]
+    while todo:
+        f = todo.pop(0)
+        if f in files or not os.path.exists(f):
+            continue
+        files.append(f)
+        with open(f) as fh:
+            todo += [os.path.join(_CSRC, n) for n in re.findall(r'#include "([^"]+)"', fh.read())]
+    return files
+
+
+# what each phase's kernels are compiled from
+PHASE_SOURCES = {"fwd": _with_headers("pool_fwd.hip"),
+                 "dedup": _with_headers("dedup.hip", "dedup_small.hip"),
+                 "bwd_update": _with_headers("reduce.hip", "reduce_wave.hip")}
 
 
 def parse():
