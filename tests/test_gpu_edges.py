@@ -65,21 +65,24 @@ def test_forward_short_and_long_bags(dtype, D, B):
         parity.run_case(ro, W, off, idx, G, B, "sum", "sgd", 0.5, 0.0, exact=dtype == "fp32", idx64=idx64)
 
 
-# rows held by 1, 2, 4 and 16 lane groups of a wavefront, and rows of several vectors per lane
+# rows held by 1, 2, 4 and 16 lane groups of a wavefront, rows of several vectors per lane, and rows in parts (the
+# last one partial, or whole)
 @pytest.mark.parametrize("dtype,D", [("fp32", 16), ("fp32", 64), ("fp32", 128), ("fp32", 256), ("fp32", 1024),
-                                     ("bf16", 128), ("bf16", 512)])
-@pytest.mark.parametrize("ids", ["one id", "skewed", "any"])
+                                     ("bf16", 128), ("bf16", 512), ("fp32", 1028), ("fp32", 2048), ("bf16", 4096)])
+@pytest.mark.parametrize("ids", ["one id", "few rows", "skewed", "any"])
 def test_forward_precision_of_long_bags(dtype, D, ids):
-    """Bags of up to 20000 ids, of one id over and over, mostly of a few hot
-    ids, or of any: with rows of one sign, an element's relative error is at
-    most one fp32 rounding for each of the pairwise additions of a round of
-    rows (3) and of the lane groups (6), one for the double sum's conversion
-    and two for the mean's scale, 2^-24 each, however long the bag."""
+    """Bags of up to 20000 ids, of one id over and over, of a table of few
+    rows, mostly of a few hot ids, or of any: with rows of one sign, an element's relative error is at
+    most one fp32 rounding for each addition in a row's way through a round (3
+    pairwise, or 8 multiply-adds where repeats are merged: rows of one or two
+    lane groups) and of the lane groups (up to 6, or 1), one for the double
+    sum's conversion and two for the mean's scale, 12 in all, 2^-24 each,
+    however long the bag."""
     import torch
     import paper_2112_02752_amd as emb
     print(f"case forward precision {dtype} D={D} {ids}", flush=True)
     rng = np.random.default_rng(D)
-    R = 3000
+    R = 20 if ids == "few rows" else 3000
     lens = np.array([1, 7, 30, 64, 65, 200, 1000, 4096, 20000])
     off = _offsets(lens)
     if ids == "one id":
