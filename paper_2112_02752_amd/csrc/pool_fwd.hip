@@ -9,9 +9,10 @@
 // lanes and reach all of them by a lane broadcast within the group (DPP for
 // groups of up to 16 lanes), with no trip through LDS.  Up to 8 rows per lane
 // group are in flight; the groups are summed across the wavefront at the end
-// (gfx950 row and half swaps).  Repeated ids of a bag are loaded again: a hot
-// row is a cache hit, and finding the repeats cost more instructions than
-// their loads.
+// (gfx950 row and half swaps).  Repeated ids of a bag are loaded again as a rule:
+// a hot row is a cache hit, and finding the repeats costs more instructions than
+// their loads.  Wide rows are the exception (merges_repeats): their repeats fill
+// the vector cache's 64 bytes a cycle.
 //
 // The rows of a round are added pairwise, as many additions as one after
 // another, and the rounds in double: one fp32 chain per lane group grows with
@@ -129,6 +130,21 @@ constexpr int slots_in_flight(int g, int nv) { return 8 / nv < 1 ? 1 : (8 / nv <
 // bags short enough to be packed one per lane group
 constexpr int kShortBag = 8;
 
+// Bags whose repeated ids are merged: rows of 64 lanes, in bags of whole chunks
+// of ids, or of enough ids to repeat the few rows of their table; rows of 32
+// lanes in the latter only.  Measured (us, every id loaded -> merged), fp32:
+//   512 values, 8192 bags of 100 ids of 10 rows     52   -> 17.9  (of 100 rows: 55 -> 47)
+//   1024 values, 8192 bags of 64 ids of one row     62   -> 11.5
+//   256 values, 4096 bags of 200 Zipf(1.2) ids      37.6 -> 32.5  (100 uniform ids: 63.2 -> 62.4)
+//   256 values, 16384 bags of 20 ids of 3 rows      14.3 -> 10.1  (10 ids: 9.8 -> 10.1)
+//   128 values, 16384 bags of 100 ids of 10 rows    29.4 -> 17.8  (40 ids of 40: 14.0 -> 14.4)
+// With few repeats it loses: 128 values, bags of 30 Zipf(1.2) ids 14.2 -> 16.4,
+// 512 bf16 values, bags of 20 Zipf(1.05) ids 9.6 -> 10.7.
+__host__ __device__ constexpr bool merges_repeats(int g, int len, uint32_t rows) {
+  const uint32_t n = (uint32_t)(len < kWave ? len : kWave);
+  return g == 64 ? len >= kWave || (len >= 16 && rows <= 2 * n) : g == 32 && len >= 32 && rows <= n;
+}
+
 struct FwdArgs {
   const void* W;
   const int32_t* offsets;
@@ -222,6 +238,88 @@ __device__ __forceinline__ void add_chunk(const char* const (&col)[NV], uint32_t
   }
 }
 
+// A chunk's distinct rows and how often each occurs, dealt to the lane groups
+// (`key`: the row of position `lane`, of n); returns their number.  Lanes are
+// classed by an 8-bit hash of the row, one ballot a bit; a lane whose row is that
+// of its class's lowest lane repeats it (a hash collision leaves a row twice).
+template <int G>
+__device__ __forceinline__ int merge_repeats(int lane, int n, uint32_t key, uint32_t& row, float& weight) {
+  constexpr int R = kWave / G;
+  const bool valid = lane < n;
+  const uint64_t all = __ballot(valid);
+  uint32_t lo = (uint32_t)all, hi = (uint32_t)(all >> 32);
+  const uint32_t h = (key * 0x9e3779b1u) >> 24;
+#pragma unroll
+  for (int b = 0; b < 8; ++b) keep_peers(h, b, lo, hi);
+  const uint64_t peers = ((uint64_t)hi << 32) | lo;
+  const int lead = valid ? (int)__builtin_ctzll(peers) : lane;
+  // (the shuffle runs on every lane: a lane switched off does not supply its value)
+  const uint32_t lead_key = (uint32_t)__shfl((int)key, lead, kWave);
+  const bool dup = valid && lead != lane && lead_key == key;
+  const uint64_t dups = __ballot(dup);
+  const bool keep = valid && !dup;
+  const uint64_t kept = __ballot(keep);
+  const int nk = (int)__popcll(kept);
+  const int rank = keep ? (int)lanes_below(kept) : nk + (int)lanes_below(~kept);
+  const int dst = rank % R * G + rank / R;
+  const int times = keep ? 1 + (lead == lane ? (int)__popcll(dups & peers) : 0) : 0;
+  row = (uint32_t)__builtin_amdgcn_ds_permute(dst << 2, (int)key);
+  weight = __int_as_float(__builtin_amdgcn_ds_permute(dst << 2, __float_as_int((float)times)));
+  return nk;
+}
+
+// A bag whose chunks' repeated rows are merged: rounds of multiply-adds, one chain
+// each, the rounds in double.  Slots past a group's last hold rows that stand in
+// and are dropped.
+template <typename TW, int G, int NV, typename TI>
+__device__ __forceinline__ void sum_merged(const char* const (&col)[NV], uint32_t rowbytes, const TI* idx, int start,
+                                           int end, uint32_t base, int lane, float (&acc)[NV][Vec<TW>::kElems]) {
+  constexpr int R = kWave / G, UN = slots_in_flight(G, NV), E = Vec<TW>::kElems;
+  const int g = lane / G;
+  double sum[NV][E] = {};
+#pragma unroll 1
+  for (int j0 = start; j0 < end; j0 += kWave) {
+    const int n = min(kWave, end - j0);
+    uint32_t row;
+    float weight;
+    // (lanes past the chunk stand in with the table's first row)
+    const int nk = merge_repeats<G>(lane, n, base + (lane < n ? (uint32_t)(int32_t)idx[j0 + lane] : 0u), row, weight);
+    const int cnt = (nk - g + R - 1) / R, nall = nk / R, nmax = (nk + R - 1) / R;
+#pragma unroll 1
+    for (int u0 = 0; u0 < nmax; u0 += UN) {
+      uint4 raw[UN][NV];
+      load_slots<TW, G, NV, UN, true, 0>(col, rowbytes, row, u0, cnt, g, raw);
+      if (u0 + UN > nall) {
+#pragma unroll
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+          for (int v = 0; v < NV; ++v)
+            if (u0 + u >= cnt) raw[u][v] = make_uint4(0u, 0u, 0u, 0u);
+      }
+      float t[NV][E] = {};
+#pragma unroll
+      for (int u = 0; u < UN; ++u) {
+        const float w = __uint_as_float(group_bcast<G>(__float_as_uint(weight), u0 + u, g));
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          float x[E];
+          Vec<TW>::widen(raw[u][v], x);
+#pragma unroll
+          for (int e = 0; e < E; ++e) t[v][e] = __builtin_fmaf(w, x[e], t[v][e]);
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v)
+#pragma unroll
+        for (int e = 0; e < E; ++e) sum[v][e] += (double)t[v][e];
+    }
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v)
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[v][e] = (float)sum[v][e];
+}
+
 template <typename TW, int G, int NV, typename TI>
 __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
   constexpr int R = kWave / G;
@@ -312,19 +410,24 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
 
   // one bag: group g takes ids g, g + R, g + 2R, ... of every 64
   const int start = __builtin_amdgcn_readfirstlane(first), end = __builtin_amdgcn_readfirstlane(last);
-  const uint32_t base = a.ro.off[table_of(m)];
-  double sum[NV][E] = {};
-  for (int j0 = start; j0 < end; j0 += kWave) {
-    const int n = min(kWave, end - j0);
-    const int k = sub * R + g;
-    const uint32_t row = k < n ? base + (uint32_t)(int32_t)idx[j0 + k] : 0u;
-    add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, sum);
-  }
+  const int t = table_of(m);
+  const uint32_t base = a.ro.off[t];
   float acc[NV][E];
+  if (merges_repeats(G, end - start, a.ro.off[t + 1] - base)) {
+    if constexpr (G >= 32) sum_merged<TW, G, NV, TI>(col, rowbytes, idx, start, end, base, lane, acc);
+  } else {
+    double sum[NV][E] = {};
+    for (int j0 = start; j0 < end; j0 += kWave) {
+      const int n = min(kWave, end - j0);
+      const int k = sub * R + g;
+      const uint32_t row = k < n ? base + (uint32_t)(int32_t)idx[j0 + k] : 0u;
+      add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, sum);
+    }
 #pragma unroll
-  for (int v = 0; v < NV; ++v)
+    for (int v = 0; v < NV; ++v)
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[v][e] = (float)sum[v][e];
+      for (int e = 0; e < E; ++e) acc[v][e] = (float)sum[v][e];
+  }
   sum_groups<G>(acc);
 
   const int L = end - start;
