@@ -205,3 +205,79 @@ def test_dedup_of_small_batches(n, rows, B):
     G = (rng.integers(-8, 9, size=(M, 4)) / 8.0).astype(np.float32)
     ro = np.concatenate([[0], np.cumsum(rows)])
     parity.run_case(ro, W, off, idx, G, B, "sum", "sgd", 0.5, 0.0, exact=True, idx64=bool(n % 2))
+
+
+def _bags_of(rng, n, M, used):
+    """Offsets of M bags that hold n ids in all, in the bags whose number is in `used` only."""
+    lens = np.zeros(M, np.int64)
+    lens[used] = np.bincount(np.sort(rng.integers(0, len(used), size=n)), minlength=len(used))
+    return _offsets(lens)
+
+
+_LAYOUTS = {
+    # one table; bags of about seven ids
+    "one table": ([40_000], lambda n: n // 7 + 1, [0]),
+    # neighbouring tables share their first positions where no bag of theirs holds an id: first, middle, last
+    "empty tables": ([50, 7, 30_000, 11, 3, 900, 1 << 20, 20], lambda n: n // 30 + 1, [2, 5, 6]),
+    # so many bags, most of them empty, that the bags around a tile are searched
+    "empty bags": ([300, 70_000], lambda n: 200_000, [0, 1]),
+    # every bag of one id
+    "one id a bag": ([1 << 22], lambda n: max(n, 32_769), [0]),
+}
+
+
+# one partial tile (more bags than one workgroup takes), exact multiples of the
+# 2048-key tiles and one key on either side, of a prefix group of 16 tiles, of
+# the 2560- and 4096-key tiles of larger batches
+_EDGES = [1, 64, 2047, 2048, 2049, 4097, 10_239, 10_240, 10_241, 32_767, 32_768, 32_769, 40_961, 511_999, 512_000,
+          512_001, 819_199, 819_200, 819_201, 1_048_577, 1_064_960, 1_064_961]
+
+
+# (and so many bags, none empty, that the samples around a tile are sampled again)
+@pytest.mark.parametrize("layout,n", [(x, n) for x in sorted(_LAYOUTS) for n in _EDGES] +
+                         [("one id a bag", 8_400_001), ("one table", 8_400_001)])
+def test_general_dedup_at_its_edges(layout, n):
+    """The dedup by sort passes, co-resident and wait-free: every integer output
+    exact, the bags through gradient rows that are sums of integers."""
+    import oracle
+    import torch
+    import paper_2112_02752_amd as emb
+    rows, bags, used = _LAYOUTS[layout]
+    T, B = len(rows), bags(n)
+    M = T * B
+    if n <= 8192 and M <= 32_768:
+        B = 32_769 // T + 1
+        M = T * B
+    print(f"case general dedup {layout} N={n} M={M}", flush=True)
+    rng = np.random.default_rng(n + M)
+    if layout == "one id a bag":
+        off = _offsets((np.arange(M) < n).astype(np.int64))
+    else:
+        off = _bags_of(rng, n, M, np.concatenate([np.arange(t * B, (t + 1) * B) for t in used]))
+    bag = np.repeat(np.arange(M), np.diff(off))
+    per = np.asarray(rows)[bag // B]
+    idx = np.minimum((per * rng.random(n) ** 3).astype(np.int64), per - 1)
+    idx = idx if n % 2 else idx.astype(np.int32)
+    ro = np.concatenate([[0], np.cumsum(rows)]).astype(np.int64)
+    ref = oracle.unique_ids(T, ro, B, off, idx.astype(np.int32))
+    G = rng.integers(-8, 9, size=(M, 4)).astype(np.float32)
+    o_gr, _ = oracle.grad_reduce(T, B, off, G, "sum", ref)
+    tables = emb.Tables(torch.empty((1, 4), dtype=torch.float32, device="cuda"), [int(x) for x in ro])
+    b = emb.Batch(torch.from_numpy(off).cuda(), torch.from_numpy(idx).cuda(), B)
+    Gd = torch.from_numpy(G).cuda()
+    d = emb.DedupBuffers("cuda", n, M, 4)
+    gr = torch.zeros((n, 4), device="cuda")
+    for concurrent in (False, True):
+        emb.unique_ids(tables, b, d.unique_keys, d.counts, d.seg_offsets, d.sort_perm, d.num_unique, d.ws,
+                       concurrent=concurrent)
+        emb.grad_reduce(tables, b, "sum", Gd, d.sort_perm, d.seg_offsets, d.unique_keys, d.num_unique, d.ws,
+                        grad_rows=gr)
+        torch.cuda.synchronize()
+        assert emb.read_status(d.ws)[0] == 0
+        U = int(d.num_unique.item())
+        assert U == ref.num_unique
+        np.testing.assert_array_equal(d.unique_keys[:U].cpu().numpy().view(np.uint32), ref.unique_keys)
+        np.testing.assert_array_equal(d.counts[:U].cpu().numpy(), ref.counts)
+        np.testing.assert_array_equal(d.seg_offsets[:U + 1].cpu().numpy(), ref.seg_offsets)
+        np.testing.assert_array_equal(d.sort_perm[:n].cpu().numpy(), ref.perm)
+        np.testing.assert_array_equal(gr[:U].cpu().numpy(), o_gr)
