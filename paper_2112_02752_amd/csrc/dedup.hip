@@ -401,7 +401,9 @@ __device__ __forceinline__ void sort_prefix_range(const PassArgs& a, uint32_t gc
 // Bag of each of this thread's positions of a tile: the bag holding position
 // j is the last m with offsets[m] <= j.  One offset in every S (S chosen so
 // the samples fit one per thread) narrows the tile's bags to a few sample
-// intervals.  Every nonempty bag of these that overlaps the tile writes its id
+// intervals; where these still hold more than kBagResample bags (batches of
+// millions of bags), samples of these intervals narrow them once more.  Every
+// nonempty bag that is left and overlaps the tile writes its id
 // at its first position in the tile, and an inclusive max-scan over the tile's
 // positions carries each id forward to the bag's other positions (bag ids grow
 // with position).  Intervals of more than kBagMarks bags (most of them empty)
@@ -416,7 +418,7 @@ __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int*
   const int nsamp = a.M / S + 1;
   int samp = 0;
   if (tid < nsamp) samp = a.offsets[min(tid * S, a.M)];
-  if (tid == 0) s_lohi[0] = s_lohi[1] = 0;
+  if (tid < 4) s_lohi[tid] = 0;
   // ids are stored plus one, so that 0 means "no bag starts here"
   for (int i = tid; i < (kSortThreads * IT); i += kSortThreads) s_work[i] = 0;
   __syncthreads();
@@ -428,8 +430,21 @@ __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int*
     atomicAdd(&s_lohi[1], (int)__popcll(le1));
   }
   __syncthreads();
-  const int m_lo = (s_lohi[0] - 1) * S;                    // a bag at or before the tile's first bag
-  const int m_hi = min((s_lohi[1] - 1) * S + S, a.M);      // an offset index at or after its last bag's end
+  int m_lo = (s_lohi[0] - 1) * S;                    // a bag at or before the tile's first bag
+  int m_hi = min((s_lohi[1] - 1) * S + S, a.M);      // an offset index at or after its last bag's end
+  if (m_hi - m_lo > kBagResample) {
+    const int S2 = (m_hi - m_lo) / kSortThreads + 1, ns2 = (m_hi - m_lo) / S2 + 1;
+    if (tid < ns2) samp = a.offsets[m_lo + tid * S2];
+    const uint64_t in0 = __ballot(tid < ns2 && samp <= p0);
+    const uint64_t in1 = __ballot(tid < ns2 && samp <= p1 - 1);
+    if (lane == 0) {
+      atomicAdd(&s_lohi[2], (int)__popcll(in0));
+      atomicAdd(&s_lohi[3], (int)__popcll(in1));
+    }
+    __syncthreads();
+    m_hi = min(m_lo + s_lohi[3] * S2, m_hi);
+    m_lo += (s_lohi[2] - 1) * S2;
+  }
   const int nst = m_hi - m_lo + 1;
   if (nst <= kBagMarks) {
     constexpr int UN = 4;
@@ -542,7 +557,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
   constexpr int DPT = (ND + kSortThreads - 1) / kSortThreads;
   __shared__ __align__(16) unsigned char s_arena[Lds::kBytes];
   __shared__ uint32_t s_wsum[NW];
-  __shared__ int s_lohi[2];
+  __shared__ int s_lohi[4];
   __shared__ uint32_t s_toff[EMB_MAX_TABLES];
   __shared__ int32_t s_first[EMB_MAX_TABLES];
   uint16_t(*s_cnt)[ND] = reinterpret_cast<uint16_t(*)[ND]>(s_arena + Lds::kCnt);

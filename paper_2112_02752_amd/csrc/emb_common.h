@@ -41,6 +41,8 @@ constexpr int kRangeTiles = 16;
 // most bags, in the sample intervals around a first-pass tile's, that the tile
 // reads one by one to find the bag of each position (above, it searches)
 constexpr int kBagMarks = 32768;
+// most bags there that a first-pass tile takes from its first samples
+constexpr int kBagResample = 8192;
 
 // prepare kernel (keys, bag ids, digit histograms)
 constexpr int kPrepThreads = 256;
