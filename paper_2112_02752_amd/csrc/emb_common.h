@@ -340,6 +340,34 @@ template <int CTRL, int ROWS = 0xf>
 __device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xf, false);
 }
+// x summed over lanes l and l ^ O (O = 32 or 16: the half and row swaps)
+template <int O>
+__device__ __forceinline__ float add_across(float x) {
+  const uint32_t b = __float_as_uint(x);
+  if constexpr (O == 32) {
+    const auto p = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  } else if constexpr (O == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  } else {
+    return x + __shfl_xor(x, O, kWave);
+  }
+}
+template <int O>
+__device__ __forceinline__ double add_across(double x) {
+  const uint32_t lo = (uint32_t)__double2loint(x), hi = (uint32_t)__double2hiint(x);
+  if constexpr (O == 32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  } else {
+    static_assert(O == 16, "halves or rows");
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    return __hiloint2double((int)h[0], (int)l[0]) + __hiloint2double((int)h[1], (int)l[1]);
+  }
+}
 // Inclusive scans of a 32-bit value over the wavefront: within rows of 16
 // lanes by shifts of 1, 2, 4 and 8, then the rows' last lanes carried on (no
 // trip through LDS, whose latency each of six shuffles would wait for).

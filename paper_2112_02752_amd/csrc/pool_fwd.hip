@@ -101,19 +101,6 @@ __device__ __forceinline__ uint32_t group_bcast_dpp(uint32_t v) {
   }
 }
 
-// x summed over lanes l and l ^ O (O = 32 or 16: the gfx950 half and row swaps)
-template <int O>
-__device__ __forceinline__ float add_across(float x) {
-  if constexpr (O == 32) {
-    const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  } else if constexpr (O == 16) {
-    const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-    return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-  } else {
-    return x + __shfl_xor(x, O, kWave);
-  }
-}
 template <int O, int NV, int E>
 __device__ __forceinline__ void sum_groups(float (&acc)[NV][E]) {
   if constexpr (O < kWave) {

@@ -3,10 +3,10 @@
 //   g_u = sum over sorted positions k of segment u of scale_{m(k)} * G[m(k)]
 //   W_r <- opt(W_r, g_u), r = unique_keys[u]
 //
-// The lane-group form, for rows of at most 64 values (wider ones, and some of
-// these, take the wave form of reduce_wave.hip).  A row of D fp32 values is
-// held by a group of G lanes (float4 per lane per vector, NV vectors), so a
-// wavefront works on 64/G rows at a time.
+// The lane-group form, for rows of at most 32 values (wider ones take the wave
+// form of reduce_wave.hip).  A row of D fp32 values is held by a group of G lanes
+// (float4 per lane per vector, NV vectors), so a wavefront works on 64/G rows at a
+// time.
 //  - Light segments (at most kChunk positions, the long tail of a skewed
 //    batch): one lane group owns the whole segment, sums its gradient rows
 //    and applies the optimizer to its table row.  Each row has exactly one
@@ -103,8 +103,8 @@ __device__ __forceinline__ void add_row(const float* src, float sc, int D, int s
   }
 }
 
-// rows of up to 256 floats a lane group keeps in flight (fewer for wider rows)
-constexpr int rows_in_flight(int nv) { return nv >= 4 ? 2 : (nv == 2 ? 4 : 8); }
+// rows a lane group keeps in flight
+constexpr int kRowsInFlight = 8;
 
 // acc[j] += sc[q][j] * src[idx[q][j]] (this lane's columns) for every (q, j)
 // with idx >= 0.  All loads are issued before the first is used, from
@@ -159,8 +159,8 @@ __device__ __forceinline__ void prefetch_row(const Upd& up, uint32_t r, int sub,
 }
 
 // Sum of squares of a row, in every lane of its group: adjacent columns first,
-// then columns 2, 4, ... apart, the order of the wave form (reduce_wave.hip),
-// so that the unfused update equals the fused one whichever form reduced.
+// then columns 2, 4, ... apart, whichever kernel updates the row, so that the
+// unfused update equals the fused one.
 template <int G, int NV>
 __device__ __forceinline__ float row_squares(const float (&acc)[NV][4]) {
 #pragma clang fp contract(off)
@@ -260,7 +260,7 @@ template <int G, int NV>
 __device__ __forceinline__ void wave_piece_sum(const RArgs& a, int lo, int hi, int g, int sub, int lane,
                                                float (&acc)[NV][4]) {
   constexpr int RPI = kWave / G;
-  constexpr int UN = rows_in_flight(NV);
+  constexpr int UN = kRowsInFlight;
   const int n = hi - lo;
   const int mbag = lane < n ? a.sorted_bag[lo + lane] : -1;
   const int up = __shfl_up(mbag, 1, kWave);
@@ -310,11 +310,11 @@ __device__ __forceinline__ void store_row(float* dst, int D, int sub, const floa
 }
 
 // positions of every light slot whose rows are loaded together
-constexpr int light_round(int nv) { return nv >= 4 ? 1 : 2; }
+constexpr int kLightRound = 2;
 // slots per lane group: one lane of the wavefront reads each segment's offsets
 constexpr int slots_for(int rpi) { return rpi * kSlots <= kWave ? kSlots : kWave / rpi; }
-// register budget of the main kernel: 5 waves per SIMD for rows of up to 256 floats (no spills)
-constexpr int reduce_waves(int nv) { return nv == 1 ? 5 : 4; }
+// register budget of the main kernel, in wavefronts per SIMD
+constexpr int kReduceWaves = 5;
 
 // Light segments, kSlots per lane group: the segments of a batch are
 // consecutive; their offsets and keys are read by one lane each, the bags of
@@ -324,7 +324,7 @@ template <typename TW, int G, int NV>
 __device__ __forceinline__ void light_batch(const RArgs& a, int ubase, int U, int g, int sub, int lane) {
   constexpr int RPI = kWave / G;
   constexpr int S = slots_for(RPI);
-  constexpr int LR = light_round(NV);
+  constexpr int LR = kLightRound;
   int ms = 0, me = 0;
   uint32_t mk = 0;
   if (lane < RPI * S && ubase + lane < U) {
@@ -402,7 +402,7 @@ __device__ __forceinline__ void light_batch(const RArgs& a, int ubase, int U, in
 }
 
 template <typename TW, int G, int NV>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(reduce_waves(NV), reduce_waves(NV)))) void k_reduce_main(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kReduceWaves, kReduceWaves))) void k_reduce_main(
     RArgs a) {
   constexpr int RPI = kWave / G;
   const int lane = threadIdx.x & (kWave - 1), g = lane / G, sub = lane % G;
@@ -475,7 +475,7 @@ template <int G, int NV>
 __device__ __forceinline__ void level2_sum(const RArgs& a, int g0, int g1, int g, int sub, WsHeader* h,
                                            float (&acc)[NV][4]) {
   constexpr int RPI = kWave / G;
-  constexpr int RR = rows_in_flight(NV) / 2 > 0 ? rows_in_flight(NV) / 2 : 1;
+  constexpr int RR = kRowsInFlight / 2;
   zero<G, NV>(acc);
 #pragma unroll 1
   for (int r0 = g0 + g; r0 < g1; r0 += RPI * RR) {
@@ -532,7 +532,7 @@ template <typename TW, int G, int NV>
 __global__ __launch_bounds__(kCombineThreads) void k_reduce_combine(RArgs a) {
   constexpr int RPI = kWave / G;
   constexpr int NWv = kCombineThreads / kWave;
-  constexpr int CU = rows_in_flight(NV);  // chunk partials of a lane group loaded together
+  constexpr int CU = kRowsInFlight;  // chunk partials of a lane group loaded together
   __shared__ int4 s_piece[kCombineChunks + 1];  // (segment, first chunk in range, start, end)
   __shared__ int s_n;
   const int tid = threadIdx.x, lane = tid & (kWave - 1), g = lane / G, sub = lane % G;
@@ -637,11 +637,6 @@ hipError_t launch_reduce_t(const RArgs& ra, int blocks_main, int blocks_comb, hi
   return hipGetLastError();
 }
 
-// Rows of 33 to 64 values are held two vectors per lane (half as many lanes
-// per row, twice as many rows per wavefront): a wavefront then carries twice
-// the light segments, which outweighs the lower occupancy (measured on rows
-// of 64 fp32 values).  Narrower rows keep one vector; wider ones take the wave
-// form.
 template <typename TW>
 hipError_t launch_reduce_dt(const RArgs& ra, int bm, int bc, hipStream_t s) {
   const int vecs = (ra.D + 3) / 4;
@@ -649,7 +644,6 @@ hipError_t launch_reduce_dt(const RArgs& ra, int bm, int bc, hipStream_t s) {
   if (vecs <= 2) return launch_reduce_t<TW, 2, 1>(ra, bm, bc, s);
   if (vecs <= 4) return launch_reduce_t<TW, 4, 1>(ra, bm, bc, s);
   if (vecs <= 8) return launch_reduce_t<TW, 8, 1>(ra, bm, bc, s);
-  if (vecs <= 16) return launch_reduce_t<TW, 8, 2>(ra, bm, bc, s);
   return hipErrorInvalidValue;
 }
 
@@ -659,8 +653,7 @@ hipError_t launch_update_t(const UArgs& ua, int blocks, hipStream_t s) {
   return hipGetLastError();
 }
 
-// (wider rows: launch_update_wave; the row-wise Adagrad sum of squares runs in
-// one order in every form, so the unfused update equals the fused one)
+// (wider rows: launch_update_wave)
 template <typename TW>
 hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
   const int vecs = (ua.up.D + 3) / 4;
@@ -672,25 +665,23 @@ hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
 }
 
 // Which form reduces.  Rows of at most 32 values: lane groups (a wavefront
-// would leave half its lanes idle).  Rows of more than 64: the wave form at
-// every size (128 bf16 values, 5.5M lookups: 510 -> 318 us; 256 fp32 values,
-// 18k lookups: 62 -> 17).  Between, with row-wise Adagrad on one table (main
+// would leave half its lanes idle).  Wider ones: the wave form (128 bf16 values,
+// 5.5M lookups: 510 -> 318 us; 256 fp32 values, 18k lookups: 62 -> 17).  Rows of
+// 64 fp32 values, row-wise Adagrad, one table of 20M rows, bags of 30 (main
 // kernel and combine, lane groups -> wave form, us; ids uniform / Zipf 0.9 /
 // 1.05 / 1.2):
-//    30k lookups   14.5 -> 11.7   20.0 -> 12.4   19.3 -> 14.6   14.3 -> 14.9
-//   120k           23.6 -> 19.0   29.0 -> 22.4   20.8 -> 19.6   17.0 -> 17.7
-//   480k           59.7 -> 52.5   53.4 -> 46.6   37.6 -> 38.2   28.8 -> 33.2
-//   720k           84.2 -> 77.1   70.3 -> 64.7   48.6 -> 46.9   36.3 -> 40.5
-//   1.2M          154.1 -> 123.1 110.4 -> 94.8   70.6 -> 65.5   52.5 -> 55.9
-// The wave form wins by its loads in flight and loses, on the most skewed ids
-// (many rows of G in the L2s), by its instructions per row.  The 50M-row
-// workload (Zipf 1.2, 492k lookups) would lose 3 us; the 8-table one (Zipf
-// 1.1, 836k) gains 8.
-constexpr int kWaveFormFew = 2048, kWaveFormMany = 10240;
-bool wave_form(int D, int nchunks) {
-  return D > 64 || (D > kLaneGroupDim && (nchunks <= kWaveFormFew || nchunks > kWaveFormMany));
-}
-
+//    30k lookups   15.2 -> 13.2   19.6 -> 13.8   18.6 -> 15.7   16.0 -> 15.8
+//   120k           25.8 -> 20.9   29.4 -> 23.9   23.5 -> 21.5   16.5 -> 19.0
+//   305k           49.4 -> 43.8   46.0 -> 38.5   33.1 -> 33.4   23.1 -> 26.8
+//   430k           66.3 -> 61.6   54.9 -> 49.7   39.9 -> 37.1   27.5 -> 29.3
+//   490k           79.8 -> 71.7   59.3 -> 53.6   43.6 -> 40.7   30.1 -> 31.8
+//   730k          130   -> 109    85.1 -> 73.8   57.7 -> 54.0   38.3 -> 38.9
+//   1.2M          212   -> 185   149   -> 122    88.4 -> 79.0   56.3 -> 54.9
+//   3.1M          481   -> 386   342   -> 247   209   -> 175   119   -> 124
+// The wave form wins by its loads in flight; where most rows of G are in the L2s
+// (the most skewed ids) its instructions per row, and its long segments' sums in
+// double, cost as much, and 2 to 4 us more at 100k to 500k lookups.  Size does not
+// tell these apart, and how skewed a batch is, the host does not know.
 int clamp_blocks(int64_t want, int lo, int hi) {
   if (want < lo) return lo;
   if (want > hi) return hi;
@@ -731,7 +722,7 @@ hipError_t launch_grad_reduce(const ReduceLaunch& p, hipStream_t s) {
   ra.up.eps = p.eps;
   ra.up.rounding = p.rounding;
   ra.up.seed = p.seed;
-  if (wave_form(p.D, ra.nchunks)) return launch_reduce_wave(ra, p.dtype, s);
+  if (p.D > kLaneGroupDim) return launch_reduce_wave(ra, p.dtype, s);
   // main: two wavefronts per chunk of sorted positions (one for its heavy
   // pieces, one for a batch of light segments), up to two full devices
   const int bm = clamp_blocks(((int64_t)ra.nchunks + 1) / 2, 1, 4096);

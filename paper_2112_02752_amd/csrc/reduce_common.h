@@ -31,7 +31,7 @@ struct RArgs {
   int32_t ncomb;        // combine blocks
   void* hdr;            // workspace header (error bits)
   int32_t N, D, pool, nchunks;
-  int32_t split;        // wave form: 2^split wavefronts share a chunk
+  int32_t split;        // wave form: 2^split wavefronts share a chunk (a block is one chunk, or four if they do not)
   Upd up;
 };
 

@@ -65,6 +65,7 @@ struct Cols {
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ __forceinline__ T load_at(uint64_t row, uint32_t off) {
   return *reinterpret_cast<const __attribute__((address_space(1))) T*>(
@@ -209,11 +210,7 @@ __device__ __forceinline__ float rows_sum(float (&r)[BT], int lane) {
     r[0] += lane_xor<O>(r[0]);
     return rows_sum<1, O * 2>(r, lane);
   } else {
-    const uint32_t x = __float_as_uint(r[0]);
-    const auto a = __builtin_amdgcn_permlane16_swap(x, x, false, false);
-    const uint32_t y = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(y, y, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+    return add_across<32>(add_across<16>(r[0]));
   }
 }
 
@@ -316,9 +313,12 @@ __device__ __forceinline__ void apply_rows(const Upd& up, float* grad_rows, uint
   }
 }
 
-// positions whose rows are loaded together: the gradient rows and the owned
-// rows of a batch stay within 64 registers (8 wavefronts per SIMD) for rows of
-// up to 256 values
+// Positions whose rows are loaded together.  The gradient rows and the owned
+// rows of a batch then take, for rows of up to 256 values, 34 to 78 vector
+// registers: 8 wavefronts per SIMD for gradient rows alone, 6 to 8 with an
+// optimizer (row-wise Adagrad 7 up to 64 values, 6 fp32 and 7 bf16 up to 128, 6
+// up to 256; up to 128 values its scalar registers are the limit as well, and
+// some of them live in lanes of a vector register).
 constexpr int batch_for(int el, int opt) {
   const int b = el <= 2 ? 8 : (el == 4 ? 4 : 2);
   return opt == EMB_OPT_ADAGRAD_ELEMENTWISE && b > 2 ? b / 2 : b;
@@ -372,17 +372,11 @@ __device__ __forceinline__ int bag_runs(int lane, int n, int bag, float scale, u
   return nruns;
 }
 
-// x summed over lanes l and l ^ O (O = 32 or 16)
-template <int O>
-__device__ __forceinline__ float add_across(float x) {
-  const uint32_t b = __float_as_uint(x);
-  const auto p = O == 32 ? __builtin_amdgcn_permlane32_swap(b, b, false, false)
-                         : __builtin_amdgcn_permlane16_swap(b, b, false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-
 // Runs in slots [U0, 16) of the four lane groups of 16 (lane 16 g + u: run
-// 4 u + g), added to this lane's four columns at `col`.  Four slots, 16 rows, are
+// 4 u + g), added to this lane's four columns at `col`, in double: a hot id's row
+// is the sum of thousands of chunks', and what they are rounded by is most of
+// its error (50M-row workload, 90k positions: 8e-5 with fp32 sums, partial rows
+// and range rows, where the row's values are about 300).  Four slots, 16 rows, are
 // loaded together; slots past the last run are read as zeros under a mask.
 template <int U0, int U, bool FULL>
 __device__ __forceinline__ void load_quad(uint64_t col, uint32_t rowbytes, uint32_t run, float weight, int nruns, int g,
@@ -397,7 +391,7 @@ __device__ __forceinline__ void load_quad(uint64_t col, uint32_t rowbytes, uint3
 }
 template <int U0 = 0>
 __device__ __forceinline__ void add_quads(uint64_t col, uint32_t rowbytes, uint32_t run, float weight, int nruns, int g,
-                                          float (&sum)[4]) {
+                                          double (&sum)[4]) {
   if constexpr (U0 < 16) {
     if (nruns <= U0 * 4) return;
     f32x4 x[4];
@@ -407,7 +401,7 @@ __device__ __forceinline__ void add_quads(uint64_t col, uint32_t rowbytes, uint3
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) sum[i] = __builtin_fmaf(wt[u], x[u][i], sum[i]);
+      for (int i = 0; i < 4; ++i) sum[i] = __builtin_fma((double)wt[u], (double)x[u][i], sum[i]);
     add_quads<U0 + 4>(col, rowbytes, run, weight, nruns, g, sum);
   }
 }
@@ -421,6 +415,8 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
   __shared__ float s_part[4 * 2][EL][kWave];  // long segments' rows of a split chunk's parts (part, slot)
   const int lane = threadIdx.x & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // a block is four chunks, or the parts of one
+  const int threads = a.split == 1 ? 2 * kWave : 4 * kWave;
   const int D = a.D;
   const Cols<EL> cl(lane, D);
   const int U = *a.num_unique;
@@ -432,7 +428,7 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
     // Adagrad with eps > 0).
     if (a.grad_rows) {
       const int64_t n = (int64_t)min(max(U, 0), a.N) * D;
-      for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+      for (int64_t i = (int64_t)blockIdx.x * threads + threadIdx.x; i < n; i += (int64_t)gridDim.x * threads)
         a.grad_rows[i] = 0.f;
     }
     return;
@@ -440,16 +436,16 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
   // the combine that follows starts from cleared level-2 rows and counters
   {
     const int nw = a.ncomb * 2 * D;
-    for (int i = (int)blockIdx.x * 256 + (int)threadIdx.x; i < nw + a.ncomb; i += (int)gridDim.x * 256) {
+    for (int i = (int)blockIdx.x * threads + (int)threadIdx.x; i < nw + a.ncomb; i += (int)gridDim.x * threads) {
       if (i < nw) a.level2[i] = 0;
       else a.arrivals[i - nw] = 0u;
     }
   }
   // this wavefront's positions [q0, q1): a chunk's, or its part `sw` of them
   // (parts of one chunk are the wavefronts of one block)
-  const int c = ((int)blockIdx.x * 4 + w) >> a.split;
+  const int c = a.split ? (int)blockIdx.x : (int)blockIdx.x * 4 + w;
   if (c >= a.nchunks) return;
-  const int sw = w & ((1 << a.split) - 1), P = kChunk >> a.split;
+  const int sw = a.split ? w : 0, P = kChunk >> a.split;
   const int p0 = c * kChunk, p1 = min(a.N, p0 + kChunk);
   const int q0 = p0 + sw * P, q1 = min(a.N, q0 + P), n = q1 - q0;  // n <= 0 past the last position
 
@@ -491,13 +487,16 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
       const int nruns = bag_runs<4>(lane, kChunk, bag, bag_scale(a, bag), 0ull, run, weight);
       const int sub = lane % 16;
       const uint64_t col = addr_of(a.G) + (sub * 4 < D ? (uint64_t)sub * 16u : 0ull);
-      float sum[4] = {0.f, 0.f, 0.f, 0.f};
+      double sum[4] = {0., 0., 0., 0.};
       add_quads(col, (uint32_t)D * 4u, run, weight, nruns, lane / 16, sum);
 #pragma unroll
       for (int i = 0; i < 4; ++i) sum[i] = add_across<32>(add_across<16>(sum[i]));
-      if (lane < 16 && sub * 4 < D)
-        store_at<f32x4>(addr_of(a.partials) + (uint64_t)c * 2 * (uint64_t)D * 4u, (uint32_t)sub * 16u,
-                        f32x4{sum[0], sum[1], sum[2], sum[3]});
+      // (in double, over the place of both of the chunk's partial rows)
+      if (lane < 16 && sub * 4 < D) {
+        const uint64_t dst = addr_of(a.partials) + (uint64_t)c * 2 * (uint64_t)D * 4u;
+        store_at<f64x2>(dst, (uint32_t)sub * 32u, f64x2{sum[0], sum[1]});
+        store_at<f64x2>(dst, (uint32_t)sub * 32u + 16u, f64x2{sum[2], sum[3]});
+      }
       return;
     }
     const int nruns = bag_runs(lane, kChunk, bag, bag_scale(a, bag), 0ull, run, weight);
@@ -684,9 +683,11 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
 
 // rows summed by a combine wavefront in one round.  (Not more: a combine is a
 // few microseconds of dependent loads, and what it unrolls has to be fetched
-// as instructions first; 64 rows a round took 16 us where 16 take less than
-// 10, with 33 KB of code instead of 8.)
-constexpr int combine_rows(int el) { return el <= 2 ? 16 : (el == 4 ? 8 : (el == 8 ? 4 : 2)); }
+// as instructions first; rows of 128 values: 64 a round took 16 us where 16 take
+// less than 10, with 33 KB of code instead of 8.  Rows of up to 64 values, 50M-row
+// workload: 16 a round 9.4 us, 32 8.7.)
+constexpr int combine_rows(int el) { return el == 1 ? 32 : (el == 2 ? 16 : (el == 4 ? 8 : (el == 8 ? 4 : 2))); }
+constexpr int level2_rows(int el) { return combine_rows(el) / 2; }
 
 // Long segments.  The block of a range of kCombineChunks chunks lists (one
 // lane per chunk) the pieces of long segments in its range: the segments
@@ -701,12 +702,25 @@ constexpr int combine_rows(int el) { return el <= 2 ? 16 : (el == 4 ? 8 : (el ==
 // another to arrive.  Rows are added in double: the partials of a hot id's
 // thousands of positions are many and large, and their roundings in fp32 would
 // be most of its row's error.
+//
+// Level-2 rows are words whose tag tells that they have arrived (the main kernel
+// clears them): doubles whose last bit is set for rows of up to 64 values, a tag
+// above a float for wider ones.
+template <int EL>
+__device__ __forceinline__ uint64_t level2_word(double x) {
+  if constexpr (EL == 1) return (uint64_t)__double_as_longlong(x) | 1ull;
+  else return ((uint64_t)kLevel2Tag << 32) | __float_as_uint((float)x);
+}
+template <int EL>
+__device__ __forceinline__ double level2_value(uint64_t w) {
+  if constexpr (EL == 1) return __longlong_as_double((int64_t)(w & ~1ull));
+  else return (double)__uint_as_float((uint32_t)w);
+}
 template <int EL>
 __device__ __forceinline__ void level2_sum(const RArgs& a, int g0, int g1, WsHeader* h, const Cols<EL>& cl,
-                                           float (&acc)[EL]) {
-  constexpr int RR = combine_rows(EL) / 2;
+                                           double (&sum)[EL]) {
+  constexpr int RR = level2_rows(EL);
   constexpr int VW = Cols<EL>::VW;
-  double sum[EL];
 #pragma unroll
   for (int v = 0; v < EL; ++v) sum[v] = 0.;
 #pragma unroll 1
@@ -729,7 +743,7 @@ __device__ __forceinline__ void level2_sum(const RArgs& a, int g0, int g1, WsHea
 #pragma unroll
       for (int q = 0; q < RR; ++q)
 #pragma unroll
-        for (int v = 0; v < EL; ++v) tags &= (uint32_t)(x[q][v] >> 32);
+        for (int v = 0; v < EL; ++v) tags &= (uint32_t)(EL == 1 ? x[q][v] : x[q][v] >> 32);
       if (__ballot(tags != kLevel2Tag) == 0ull) break;
       if (wait_over(h, h->gen, t0, ++spins)) {
         flag_timeout(h, h->gen, kSiteCombine, kCombineError);
@@ -741,11 +755,9 @@ __device__ __forceinline__ void level2_sum(const RArgs& a, int g0, int g1, WsHea
     for (int q = 0; q < RR; ++q)
       if (r0 + q < g1) {
 #pragma unroll
-        for (int v = 0; v < EL; ++v) sum[v] += (double)__uint_as_float((uint32_t)x[q][v]);
+        for (int v = 0; v < EL; ++v) sum[v] += level2_value<EL>(x[q][v]);
       }
   }
-#pragma unroll
-  for (int v = 0; v < EL; ++v) acc[v] = (float)sum[v];
 }
 
 template <typename TW, int EL, int OPT>
@@ -786,28 +798,55 @@ __global__ __launch_bounds__(kCombineThreads) void k_combine_wave(RArgs a) {
     const uint64_t wrow = addr_of(a.up.W) + (uint64_t)key * ((uint64_t)D * sizeof(TW));
     own[0].load(a.up, wrow, key, cl);
     const float h = OPT == EMB_OPT_ADAGRAD_ROWWISE ? a.up.state[key] : 0.f;
-    float acc1[1][EL];
-    float(&acc)[EL] = acc1[0];
     double sum[EL];
 #pragma unroll
     for (int v = 0; v < EL; ++v) sum[v] = 0.;
-    // lane i: the address of the piece's i-th partial (the last one's past it)
-    const int ci = cf + min(lane, np - 1);
-    const uint64_t prow =
-        addr_of(a.partials) + ((uint64_t)ci * 2 + (ci == cs && st != ci * kChunk ? 1 : 0)) * ((uint64_t)D * 4u);
+    if constexpr (EL == 1) {
+      // The piece's whole chunks (that lie, with the position after them, in the
+      // segment) left doubles; its first chunk, if the segment starts within it,
+      // and its last, if the segment ends in it, floats.
+      const bool part0 = st > cf * kChunk, part1 = en <= (cl1 + 1) * kChunk;
+      const int w0 = cf + (part0 ? 1 : 0), w1 = cl1 + (part1 ? 0 : 1);
+      const uint64_t stride = (uint64_t)D * 8u, rows = addr_of(a.partials);
+      const float x0 = load_at<float>(rows + (uint64_t)cf * stride + (uint64_t)D * 4u, cl.at[0] * 4u);
+      const float x1 = load_at<float>(rows + (uint64_t)cl1 * stride, cl.at[0] * 4u);
+      // (rounds of 32 rows, whole ranges' in two; what is left, and short pieces, in rounds of 8)
+      int i0 = w0;
 #pragma unroll 1
-    for (int i0 = 0; i0 < np; i0 += CU) {
-      float x[CU][EL];
+      for (; i0 + CU <= w1; i0 += CU) {
+        double x[CU];
 #pragma unroll
-      for (int q = 0; q < CU; ++q) load_f32<EL>(lane_value(prow, i0 + q), cl, x[q]);
-      if (np - i0 < CU) drop_rows<EL, CU>(x, np - i0);
+        for (int q = 0; q < CU; ++q) x[q] = load_at<double>(rows + (uint64_t)(i0 + q) * stride, cl.at[0] * 8u);
 #pragma unroll
-      for (int q = 0; q < CU; ++q)
+        for (int q = 0; q < CU; ++q) sum[0] += x[q];
+      }
+#pragma unroll 1
+      for (; i0 < w1; i0 += 8) {
+        double x[8];
 #pragma unroll
-        for (int v = 0; v < EL; ++v) sum[v] += (double)x[q][v];
+        for (int q = 0; q < 8; ++q)
+          x[q] = load_at<double>(rows + (uint64_t)min(i0 + q, w1 - 1) * stride, cl.at[0] * 8u);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum[0] += i0 + q < w1 ? x[q] : 0.;
+      }
+      sum[0] += (part0 ? (double)x0 : 0.) + (part1 ? (double)x1 : 0.);
+    } else {
+      // lane i: the address of the piece's i-th partial (the last one's past it)
+      const int ci = cf + min(lane, np - 1);
+      const uint64_t prow =
+          addr_of(a.partials) + ((uint64_t)ci * 2 + (ci == cs && st != ci * kChunk ? 1 : 0)) * ((uint64_t)D * 4u);
+#pragma unroll 1
+      for (int i0 = 0; i0 < np; i0 += CU) {
+        float x[CU][EL];
+#pragma unroll
+        for (int q = 0; q < CU; ++q) load_f32<EL>(lane_value(prow, i0 + q), cl, x[q]);
+        if (np - i0 < CU) drop_rows<EL, CU>(x, np - i0);
+#pragma unroll
+        for (int q = 0; q < CU; ++q)
+#pragma unroll
+          for (int v = 0; v < EL; ++v) sum[v] += (double)x[q][v];
+      }
     }
-#pragma unroll
-    for (int v = 0; v < EL; ++v) acc[v] = (float)sum[v];
     const int bs = cs / kCombineChunks, be = ce / kCombineChunks;  // combine blocks of the segment
     bool done = bs == be;
     if (!done) {
@@ -815,12 +854,15 @@ __global__ __launch_bounds__(kCombineThreads) void k_combine_wave(RArgs a) {
       uint64_t* dst = a.level2 + ((size_t)blk * 2 + (blk == bs ? 1 : 0)) * D;
 #pragma unroll
       for (int v = 0; v < EL; ++v)
-        if (cl.ok[v / VW]) st_u64(dst + cl.at[v / VW] + v % VW, ((uint64_t)kLevel2Tag << 32) | __float_as_uint(acc[v]));
+        if (cl.ok[v / VW]) st_u64(dst + cl.at[v / VW] + v % VW, level2_word<EL>(sum[v]));
       uint32_t old = 0;
       if (lane == 0) old = atomic_add_u32(&a.arrivals[bs], 1u);
       done = lane_value(old, 0) == (uint32_t)(be - bs);
-      if (done) level2_sum<EL>(a, bs, be + 1, reinterpret_cast<WsHeader*>(a.hdr), cl, acc);
+      if (done) level2_sum<EL>(a, bs, be + 1, reinterpret_cast<WsHeader*>(a.hdr), cl, sum);
     }
+    float acc1[1][EL];
+#pragma unroll
+    for (int v = 0; v < EL; ++v) acc1[0][v] = (float)sum[v];
     if (done) apply_rows<TW, EL, OPT, 1>(a.up, a.grad_rows, 1u, u, key, wrow, h, acc1, own, cl, lane);
   }
 }
@@ -865,15 +907,29 @@ __global__ __launch_bounds__(256) void k_update_wave(UArgs a) {
   }
 }
 
-// 104 bf16 values, element-wise Adagrad, 4300 chunks: 81 us with one wavefront
-// to a chunk, 67 with four; 256 fp32 values, 282 chunks: 28 and 17; 128 bf16
-// values, 86k chunks: 318 and 400; 64 fp32 values, 13k chunks: 50 and 60
-constexpr int kSplitChunks = 5000;
+// Chunks of a batch up to which four, and two, wavefronts share each.  One
+// wavefront to a chunk fills the device once with 7000 to 8000 chunks (7 or 8 to
+// a SIMD), and a few chunks more are a second round of few wavefronts; the parts
+// of a chunk cost its bounds again.  Main kernel and combine, row-wise Adagrad,
+// one / two / four wavefronts to a chunk (us):
+//   64 fp32 values     Zipf 1.2               Zipf 1.05              uniform ids
+//     2.8k chunks      26.1 / 23.6 / 21.0     28.8 / 26.9 / 25.0     28.6 / 28.3 / 27.9
+//     4.8k             29.3 / 25.9 / 26.4     35.6 / 31.0 / 32.0     46.3 / 45.0 / 43.5
+//     8.6k             35.5 / 32.3 / 34.2     46.3 / 42.5 / 43.6     85.6 / 82.2 / 81.9
+//    15.3k             48.5 / 45.1 / 49.9     68.8 / 65.0 / 65.6    136.0 / 133.5 / 135.7
+//    19k               52.4 / 50.2 / -        68.4 / 66.0 / -       125.4 / 121.7 / -
+//    38k               88.5 / 88.5 / -       116.3 / 113.8 / -      202.6 / 206.3 / -
+//   512 bf16 values
+//     5.7k            111.3 / 106.3 / 99.8   141.7 / 133.9 / 128.2  206.4 / 203.7 / 199.5
+//     9.6k            175.2 / 164.8 / 158.6  221.3 / 213.7 / 205.9  331.5 / 322.1 / 319.0
+constexpr int split_four(int el) { return el == 1 ? 5000 : 8192; }
+constexpr int kSplitTwo = 20480;
 
 template <typename TW, int EL, int OPT>
 hipError_t launch_reduce_t(const RArgs& ra, hipStream_t s) {
-  const int64_t blocks = (((int64_t)ra.nchunks << ra.split) + 3) / 4;
-  hipLaunchKernelGGL((k_reduce_wave<TW, EL, OPT>), dim3((unsigned)blocks), dim3(256), 0, s, ra);
+  const int blocks = ra.split ? ra.nchunks : (ra.nchunks + 3) / 4;
+  const int waves = ra.split == 1 ? 2 : 4;
+  hipLaunchKernelGGL((k_reduce_wave<TW, EL, OPT>), dim3((unsigned)blocks), dim3((unsigned)(waves * kWave)), 0, s, ra);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_combine_wave<TW, EL, OPT>), dim3((unsigned)ra.ncomb), dim3(kCombineThreads), 0, s, ra);
@@ -928,10 +984,7 @@ hipError_t launch_update_dt(const UArgs& ua, hipStream_t s) {
 
 hipError_t launch_reduce_wave(const RArgs& args, int dtype, hipStream_t s) {
   RArgs ra = args;
-  // few chunks: four wavefronts to a chunk, so that the device has work (a
-  // chunk's batches of rows are a serial chain); many: one, so that a chunk's
-  // bounds are read once
-  ra.split = ra.nchunks <= kSplitChunks ? 2 : 0;
+  ra.split = ra.nchunks <= split_four(ra.D <= 64 ? 1 : 2) ? 2 : (ra.nchunks <= kSplitTwo ? 1 : 0);
   return dtype == EMB_FP32 ? launch_reduce_dt<float>(ra, s) : launch_reduce_dt<uint16_t>(ra, s);
 }
 

@@ -165,11 +165,31 @@ def test_reduce_segment_lengths(dtype, D, name):
                 np.testing.assert_array_equal(got[0][2].state_rows(keys), got[1][2].state_rows(keys))
 
 
+@pytest.mark.parametrize("dtype,D", [("fp32", 36), ("bf16", 72), ("fp32", 132)])
+@pytest.mark.parametrize("chunks", [5000, 5001, 8192, 8193, 20480, 20481])
+def test_reduce_split_of_chunks(dtype, D, chunks):
+    """Batches on both sides of the sizes where four, two and one wavefronts
+    share a chunk, segments of all lengths around a chunk's and its parts'; the
+    gradient rows are integers, their sums exact."""
+    print(f"case reduce split {dtype} D={D} chunks={chunks}", flush=True)
+    rng = np.random.default_rng(D + chunks)
+    N = chunks * 64 - 7
+    lens = rng.choice([1, 1, 1, 2, 3, 15, 16, 17, 31, 32, 33, 63, 64, 65, 66, 130, 700, 9000], size=N)
+    lens = lens[:int(np.searchsorted(np.cumsum(lens), N)) + 1]
+    lens[-1] -= int(lens.sum()) - N
+    M = N // 9
+    off, idx = _segments_case(rng, lens, M, 1)
+    W = _dyadic(rng, (len(lens), D), dtype)
+    G = rng.integers(-16, 17, size=(M, D)).astype(np.float32)
+    parity.run_case([0, len(lens)], W, off, idx, G, M, "sum", "sgd", 0.5, 0.0, exact=dtype == "fp32")
+
+
 @pytest.mark.parametrize("D", [36, 48, 64])
-@pytest.mark.parametrize("n", [2048 * 64, 2048 * 64 + 1, 10240 * 64 + 1])
+@pytest.mark.parametrize("n", [2048 * 64, 2048 * 64 + 1, 5000 * 64 + 1, 10240 * 64 + 1, 20480 * 64 + 1])
 def test_unfused_equals_fused_in_both_forms(D, n):
-    """Batches on both sides of the sizes where rows of 33 to 64 values change
-    the form of their reduce; the separate update has one form."""
+    """Batches on both sides of the sizes where chunks are shared by four, two
+    and one wavefronts: a row's sum of squares is formed in one order, whichever
+    kernel updates it."""
     print(f"case unfused forms D={D} N={n}", flush=True)
     rng = np.random.default_rng(n + D)
     rows, B = 30000, n // 20
