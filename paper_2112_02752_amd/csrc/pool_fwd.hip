@@ -15,10 +15,13 @@
 // the vector cache's 64 bytes a cycle.
 //
 // The rows of a round are added pairwise, as many additions as one after
-// another, and the rounds in double: one fp32 chain per lane group grows with
-// the bag, and adding the same row over and over rounds the same way each time
-// (one id 4096 times in a bag, rows of 256 fp32 values: 3e-5 off in the chain,
-// exact now; 4096 Zipf(1.2) ids, 64 values: 1.9e-6 and 4e-8).
+// another; rounds are added in double where a row takes 32 lanes or more, and in
+// fp32 within a chunk of 64 ids and then across chunks where it takes fewer (in
+// double 26 tables of 128 bf16 values take 140 us for 137).  One fp32 chain per
+// lane group grows with the bag, and adding the same row over and over rounds the
+// same way each time.  One id 4096 times in a bag, rows of 256 / 64 fp32 values:
+// 3e-5 / 8e-6 off in the chain, exact / 5e-7 now; 4096 Zipf(1.2) ids, 64 values:
+// 1.9e-6 and 6e-8.
 //
 // What bounds it: the rows the L2s miss, once the instructions per row are few
 // enough.  Merging repeats by hash classes, LDS shuffles and a select per
@@ -34,6 +37,8 @@
 // neighbours (four in all, or as many as there are lane groups) hold at most
 // kShortBag ids each (one round of loads per lane group), the first of these
 // wavefronts sums one bag per lane group and the others leave at once.
+#include <type_traits>
+
 #include "emb_common.h"
 #include "kernels.h"
 
@@ -180,7 +185,7 @@ __device__ __forceinline__ void sum_round(const uint4 (&raw)[UN][NV], int v, flo
     for (int e = 0; e < Vec<TW>::kElems; ++e) o[e] += x[e];
   }
 }
-// (A: float where a bag is one round, else double)
+// (A: float for one or two rounds, else double)
 template <typename TW, int G, int NV, int UN, bool FULL, int U0, typename A>
 __device__ __forceinline__ void add_slots(const char* const (&col)[NV], uint32_t rowbytes, uint32_t row, int u0,
                                           int cnt, int g, A (&acc)[NV][Vec<TW>::kElems]) {
@@ -403,12 +408,22 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
   if (merges_repeats(G, end - start, a.ro.off[t + 1] - base)) {
     if constexpr (G >= 32) sum_merged<TW, G, NV, TI>(col, rowbytes, idx, start, end, base, lane, acc);
   } else {
-    double sum[NV][E] = {};
+    // (chunks of one or two rounds: their sums, and the bag's of these, in fp32)
+    typename std::conditional<(G >= 32), double, float>::type sum[NV][E] = {};
     for (int j0 = start; j0 < end; j0 += kWave) {
       const int n = min(kWave, end - j0);
       const int k = sub * R + g;
       const uint32_t row = k < n ? base + (uint32_t)(int32_t)idx[j0 + k] : 0u;
-      add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, sum);
+      if constexpr (G >= 32) {
+        add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, sum);
+      } else {
+        float t[NV][E] = {};
+        add_chunk<TW, G, NV>(col, rowbytes, row, (n - g + R - 1) / R, n / R, (n + R - 1) / R, g, t);
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+#pragma unroll
+          for (int e = 0; e < E; ++e) sum[v][e] += t[v][e];
+      }
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v)

@@ -72,12 +72,13 @@ def test_forward_short_and_long_bags(dtype, D, B):
 @pytest.mark.parametrize("ids", ["one id", "few rows", "skewed", "any"])
 def test_forward_precision_of_long_bags(dtype, D, ids):
     """Bags of up to 20000 ids, of one id over and over, of a table of few
-    rows, mostly of a few hot ids, or of any: with rows of one sign, an element's relative error is at
-    most one fp32 rounding for each addition in a row's way through a round (3
-    pairwise, or 8 multiply-adds where repeats are merged: rows of one or two
-    lane groups) and of the lane groups (up to 6, or 1), one for the double
-    sum's conversion and two for the mean's scale, 12 in all, 2^-24 each,
-    however long the bag."""
+    rows, mostly of a few hot ids, or of any: with rows of one sign, an element's
+    relative error is at most one fp32 rounding, 2^-24, for each addition in a
+    row's way: a round (3 pairwise and 1 of two rounds; or 8 multiply-adds where
+    repeats are merged: rows of one or two lane groups), the lane groups (up to
+    2, 6 without a second round, or 1), one for a double sum's conversion and two
+    for the mean's scale, 12 in all, and for rows of fewer than 32 lanes one for
+    each further chunk of 64 ids."""
     import torch
     import paper_2112_02752_amd as emb
     print(f"case forward precision {dtype} D={D} {ids}", flush=True)
@@ -103,7 +104,8 @@ def test_forward_precision_of_long_bags(dtype, D, ids):
             n = np.bincount(idx[off[m]:off[m + 1]], minlength=R).astype(np.float64)
             ref = (n @ rows) / (L if pool == "mean" else 1)
             err = np.abs(out[m].cpu().numpy().astype(np.float64) - ref) / ref
-            assert err.max() <= 12 * 2.0 ** -24, (L, pool, err.max())
+            wide = D * (4 if dtype == "fp32" else 2) > 256
+            assert err.max() <= (12 + (0 if wide else L // 64)) * 2.0 ** -24, (L, pool, err.max())
 
 
 def _segments_case(rng, seg_lens, M, repeat):
