@@ -402,13 +402,14 @@ __device__ __forceinline__ void sort_prefix_range(const PassArgs& a, uint32_t gc
 // j is the last m with offsets[m] <= j.  One offset in every S (S chosen so
 // the samples fit one per thread) narrows the tile's bags to a few sample
 // intervals; where these still hold more than kBagResample bags (batches of
-// millions of bags), samples of these intervals narrow them once more.  Every
+// millions of bags, whose passes read their offsets: RESAMPLE), samples of these
+// intervals narrow them once more.  Every
 // nonempty bag that is left and overlaps the tile writes its id
 // at its first position in the tile, and an inclusive max-scan over the tile's
 // positions carries each id forward to the bag's other positions (bag ids grow
 // with position).  Intervals of more than kBagMarks bags (most of them empty)
 // are searched instead.  `s_work` holds one int per position of the tile.
-template <int IT>
+template <int IT, bool RESAMPLE>
 __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int* s_lohi, int32_t* s_work,
                                                uint32_t* s_wmax, int32_t (&bag)[IT]) {
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & (kWave - 1);
@@ -432,7 +433,7 @@ __device__ __forceinline__ void find_tile_bags(const PassArgs& a, int tile, int*
   __syncthreads();
   int m_lo = (s_lohi[0] - 1) * S;                    // a bag at or before the tile's first bag
   int m_hi = min((s_lohi[1] - 1) * S + S, a.M);      // an offset index at or after its last bag's end
-  if (m_hi - m_lo > kBagResample) {
+  if (RESAMPLE && m_hi - m_lo > kBagResample) {
     const int S2 = (m_hi - m_lo) / kSortThreads + 1, ns2 = (m_hi - m_lo) / S2 + 1;
     if (tid < ns2) samp = a.offsets[m_lo + tid * S2];
     const uint64_t in0 = __ballot(tid < ns2 && samp <= p0);
@@ -662,7 +663,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
       }
       publish_counts();
     }
-    find_tile_bags<IT>(a, tile, s_lohi, reinterpret_cast<int32_t*>(s_keys), s_wsum, bag);
+    find_tile_bags<IT, !CORE>(a, tile, s_lohi, reinterpret_cast<int32_t*>(s_keys), s_wsum, bag);
     if constexpr (!CORE) {
 #pragma unroll
       for (int i = 0; i < IT; ++i) {
