@@ -127,9 +127,9 @@ struct PassArgs {
   uint64_t* rows;          // published tile counts (tag << 32 | count): [tiles][status_stride]
   uint64_t* grp;           // published group sums, same form: [groups][status_stride]
   WsHeader* hdr;
-  // first pass with co-resident tiles: the bag of every position is found here
-  // (offsets, idx, ro, B, M); the first pass also clears the unique scan's
-  // look-back words
+  // first pass of one batch: the ids are read, their tables' first rows added and
+  // the bag of every position found here (offsets, idx, ro, B, M); it also clears
+  // the unique scan's look-back words
   int32_t search_bags;
   const int32_t* offsets;
   const void* idx;
@@ -137,7 +137,7 @@ struct PassArgs {
   TableOffsets ro;
   int32_t B, M, T;
   int32_t tstep;           // table_step(T)
-  uint32_t b_magic;        // floor(2^32 / B) (B > 1)
+  uint32_t b_magic;        // bag_magic(B)
   uint64_t* uniq_status;
   int32_t uniq_tiles;
   int32_t N, ntiles, shift, bits, pass, status_stride;
@@ -231,23 +231,19 @@ __device__ __forceinline__ void poll_batch(const uint64_t* base, int stride, int
 // The last tile of a group of kPrefixGroup tiles reads the group's published
 // counts for digit d (one batch), publishes the group's sum and returns the
 // in-group exclusive prefixes of the group's tiles as 16-bit pairs (a group
-// of co-resident tiles holds fewer than 2^16 keys before its last tile), and
-// its own.
+// of co-resident tiles holds fewer than 2^16 keys before its last tile).
 static_assert((kPrefixGroup - 1) * kSortThreads * kSortItemsWide < 65536, "in-group prefixes fit 16 bits");
 __device__ __forceinline__ void group_counts(const uint64_t* rows, uint64_t* grp, int stride, int g, int g0, int g1,
                                              int d, uint64_t tag, WsHeader* h, uint32_t gcall, uint32_t site,
-                                             uint32_t (&pk)[kPrefixGroup / 2],
-                                             uint32_t& last_pre) {
+                                             uint32_t (&pk)[kPrefixGroup / 2]) {
   uint64_t v[kPrefixGroup];
   const int n = g1 - g0;
   poll_batch<kPrefixGroup>(rows, stride, g0, n, d, tag, h, gcall, site, v);
   uint32_t run = 0;
-  last_pre = 0;
 #pragma unroll
   for (int i = 0; i < kPrefixGroup; ++i) {
     if (i % 2 == 0) pk[i / 2] = run;
     else pk[i / 2] |= run << 16;
-    if (i == n - 1) last_pre = run;
     if (i < n) run += word_count(v[i]);
   }
   st_u64(grp + (size_t)g * stride + d, word_make(tag, run));
@@ -296,9 +292,9 @@ __device__ __forceinline__ void sort_prefix_block(const PassArgs& a, uint32_t gc
   for (int k = 0; k < DPT; ++k) {
     const int d = tid + k * kSortThreads;
     if (d < ND) {
-      uint32_t pk[kPrefixGroup / 2], unused;
+      uint32_t pk[kPrefixGroup / 2];
       group_counts(a.rows, a.grp, a.status_stride, g, g0, g1, d, tag, a.hdr, gcall,
-                   kSiteGroupCounts | ((uint32_t)a.pass << 4), pk, unused);
+                   kSiteGroupCounts | ((uint32_t)a.pass << 4), pk);
 #pragma unroll
       for (int j = 0; j < kPrefixGroup / 2; ++j) s_pre[j * ND + d] = pk[j];
     }
@@ -668,10 +664,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_sort_pass(PassArgs a) {
 #pragma unroll
       for (int i = 0; i < IT; ++i) {
         if (a.T > 1) {
-          // the division by B as a multiplication, one too few at most
-          uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag[i], a.b_magic) : (uint32_t)bag[i];
-          if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag[i]) ++t;
-          key[i] += s_toff[t];
+          key[i] += s_toff[table_of_bag((uint32_t)bag[i], a.B, a.b_magic)];
         }
         dig[i] = (key[i] >> a.shift) & mask;
       }
@@ -1339,8 +1332,8 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
   // Co-resident passes, when every tile of a pass and its prefix blocks fit
   // one block per compute unit (coresident_limit): tile = block index, bags
   // found by the first pass, two-level published-count prefix, with the
-  // smallest tiles that fit.  Otherwise a prepare kernel (bags, keys) and
-  // 4096-key tiles, each pass preceded by its tile counts and column scan.
+  // smallest tiles that fit.  Otherwise 4096-key tiles, each pass preceded by its
+  // tile counts and column scan.
   // A co-resident pass also runs its prefix blocks after the tiles: one per
   // group of kPrefixGroup tiles for the first pass, one per kRangeDigits
   // digits for the later ones (their digit totals are counted during the
@@ -1427,7 +1420,7 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
     xa.M = p.M;
     xa.T = p.T;
     xa.tstep = table_step(p.T);
-    xa.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
+    xa.b_magic = bag_magic(p.B);
     xa.uniq_status = reinterpret_cast<uint64_t*>(ws + L.uniq_status);
     xa.uniq_tiles = uniq_tiles;
     xa.hdr = hdr;
@@ -1664,8 +1657,9 @@ hipError_t launch_dedup_group(const GroupDedupLaunch& p, hipStream_t s) {
   const int n = p.n;
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   hipError_t e = hipSuccess;
-  uint32_t* keys_built = reinterpret_cast<uint32_t*>(ws + L.keys_built);
-  int32_t* bag_of = reinterpret_cast<int32_t*>(ws + L.bag_of);
+  // (the first pass reads these before the second writes there)
+  uint32_t* keys_built = reinterpret_cast<uint32_t*>(ws + L.keys_b);
+  int32_t* bag_of = reinterpret_cast<int32_t*>(ws + L.bags_b);
   uint32_t* sorted_keys = reinterpret_cast<uint32_t*>(ws + L.sorted_keys);
   int32_t* group_perm = reinterpret_cast<int32_t*>(ws + L.group_perm);
   int32_t* sorted_bag = reinterpret_cast<int32_t*>(ws + L.sorted_bag);

@@ -29,7 +29,7 @@ struct SmallArgs {
   const int32_t* offsets;
   const void* idx;
   int32_t idx64, T, B, M, N;
-  uint32_t b_magic;  // floor(2^32 / B)
+  uint32_t b_magic;  // bag_magic(B)
   int32_t passes, shift[kMaxPasses], bits[kMaxPasses];
   uint32_t* unique_keys;
   int32_t* counts;
@@ -95,9 +95,7 @@ __global__ __launch_bounds__(kThreads) void k_dedup_small(SmallArgs a) {
     if (pos[i] < a.N) {
       s_bag[pos[i]] = (int32_t)m;
       if (a.T > 1) {
-        // table of the bag: the division by B as a multiplication, one too few at most
-        uint32_t t = a.B > 1 ? __umulhi(m, a.b_magic) : m;
-        if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= m) ++t;
+        const uint32_t t = table_of_bag(m, a.B, a.b_magic);
         key[i] += s_toff[t < (uint32_t)a.T ? t : 0u];
       }
     }
@@ -244,7 +242,7 @@ hipError_t launch_dedup_small(const DedupLaunch& p, hipStream_t s) {
   a.B = p.B;
   a.M = p.M;
   a.N = (int32_t)p.N;
-  a.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
+  a.b_magic = bag_magic(p.B);
   a.passes = p.plan.passes;
   for (int i = 0; i < kMaxPasses; ++i) {
     a.shift[i] = p.plan.shift[i];

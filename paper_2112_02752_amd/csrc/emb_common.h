@@ -44,7 +44,7 @@ constexpr int kBagMarks = 32768;
 // most bags there that a first-pass tile takes from its first samples
 constexpr int kBagResample = 8192;
 
-// prepare kernel (keys, bag ids, digit histograms)
+// a group dedup's prepare kernel (keys and bag ids)
 constexpr int kPrepThreads = 256;
 constexpr int kPrepMaxBags = 1024;     // bags of one block (offsets staged in LDS)
 constexpr int kPrepPositions = 2048;   // positions a block aims at
@@ -86,7 +86,7 @@ static_assert(sizeof(WsHeader) == 256, "header is one 256-byte block");
 // tags differ.
 struct WsLayout {
   // front (offsets from the workspace base)
-  size_t hdr, totals, keys_built, keys_a, keys_b, vals_a, vals_b, bags_a, bags_b, bag_of, sorted_keys, sorted_bag,
+  size_t hdr, totals, keys_a, keys_b, vals_a, vals_b, bags_a, bags_b, sorted_keys, sorted_bag,
       group_perm, uniq_status, tile_counts, chunk_seg, partials, level2, arrivals, front;
   // back (offsets from the back base)
   size_t pass_status, rows, grp, later, back;
@@ -110,8 +110,6 @@ inline WsLayout ws_layout(int64_t N, int64_t M, int32_t D) {
   L.totals = off;
   off = align256(off + sizeof(uint32_t) * kMaxPasses * kMaxDigits);
   const size_t n4 = sizeof(uint32_t) * (size_t)n;
-  L.keys_built = off;
-  off = align256(off + n4);
   L.keys_a = off;
   off = align256(off + n4);
   L.keys_b = off;
@@ -123,8 +121,6 @@ inline WsLayout ws_layout(int64_t N, int64_t M, int32_t D) {
   L.bags_a = off;
   off = align256(off + n4);
   L.bags_b = off;
-  off = align256(off + n4);
-  L.bag_of = off;
   off = align256(off + n4);
   L.sorted_keys = off;
   off = align256(off + n4);
@@ -175,6 +171,15 @@ inline char* ws_back(void* ws, size_t ws_bytes, const WsLayout& L) {
 struct TableOffsets {
   uint32_t off[EMB_MAX_TABLES + 1];
 };
+
+// Table of a bag, with B bags a table: the division by B as a multiplication by
+// magic = floor(2^32 / B), whose result is one too small at most.
+inline uint32_t bag_magic(int32_t B) { return B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)B) : 0u; }
+__device__ __forceinline__ uint32_t table_of_bag(uint32_t bag, int32_t B, uint32_t magic) {
+  if (B <= 1) return bag;
+  const uint32_t t = __umulhi(bag, magic);
+  return (t + 1u) * (uint32_t)B <= bag ? t + 1u : t;
+}
 
 // Batches deduplicated by one workgroup: keys that fit its LDS, and bags few
 // enough to be read by it (bags may be empty, so their number is not bounded by

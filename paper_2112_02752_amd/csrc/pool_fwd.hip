@@ -142,7 +142,7 @@ struct FwdArgs {
   const int32_t* offsets;
   const void* idx;
   int32_t B, M, D, pool;
-  uint32_t b_magic;  // floor(2^32 / B) (B > 1)
+  uint32_t b_magic;  // bag_magic(B)
   float* out;
   TableOffsets ro;
 };
@@ -335,13 +335,6 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
     col[v] = static_cast<const char*>(a.W) + (size_t)(c0 < a.D ? c0 : 0) * sizeof(TW);
   }
 
-  // table of a bag: the division by B as a multiplication, one too few at most
-  auto table_of = [&](int bag) {
-    uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag, a.b_magic) : (uint32_t)bag;
-    if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag) ++t;
-    return (int)t;
-  };
-
   int first, last;  // the bag's ids
   // the P bags of this wavefront and its neighbours, when they are all there
   const int m0 = m - w % P;
@@ -366,7 +359,7 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
           len = g == i ? o[i + 1] - o[i] : len;
         }
         if (g >= P) len = 0;
-        const int t = table_of(m0);
+        const int t = (int)table_of_bag((uint32_t)m0, a.B, a.b_magic);
         // P bags lie in at most two tables
         const uint32_t base = m0 + g < (t + 1) * a.B ? a.ro.off[t] : a.ro.off[t + 1];
         const uint32_t row = sub < len ? base + (uint32_t)(int32_t)idx[start + sub] : 0u;
@@ -402,7 +395,7 @@ __global__ __launch_bounds__(256) void k_pool_fwd(FwdArgs a) {
 
   // one bag: group g takes ids g, g + R, g + 2R, ... of every 64
   const int start = __builtin_amdgcn_readfirstlane(first), end = __builtin_amdgcn_readfirstlane(last);
-  const int t = table_of(m);
+  const int t = (int)table_of_bag((uint32_t)m, a.B, a.b_magic);
   const uint32_t base = a.ro.off[t];
   float acc[NV][E];
   if (merges_repeats(G, end - start, a.ro.off[t + 1] - base)) {
@@ -461,7 +454,7 @@ hipError_t launch_t(const FwdLaunch& p, hipStream_t s) {
   a.M = p.M;
   a.D = p.D;
   a.pool = p.pool;
-  a.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
+  a.b_magic = bag_magic(p.B);
   a.out = p.out;
   a.ro = p.ro;
   // the index type (int32 or int64) is a template argument: no per-load branch

@@ -54,7 +54,7 @@ struct RouteArgs {
   TableOffsets ro;
   ShardBounds sb;
   int32_t B, M, W, owner_bits, bags_per_block, nblocks;
-  uint32_t b_magic;  // floor(2^32 / B) (B > 1)
+  uint32_t b_magic;  // bag_magic(B)
   int32_t N;
   int32_t* counts;  // [W][nblocks]: a block's count of each owner, then its base within the owner's range
   int32_t* send_counts;
@@ -100,13 +100,10 @@ __device__ __forceinline__ int owner_of(const uint32_t* s_sb, int W, uint32_t ke
 // positions a wavefront loads ids for before it routes the first of them
 constexpr int kRouteBatch = 4;
 
-// first global row of a bag's table (one table: no lookup; otherwise the
-// division by B as a multiplication, one too few at most)
+// first global row of a bag's table (one table: no lookup)
 __device__ __forceinline__ uint32_t table_row(const RouteArgs& a, int bag) {
   if (a.M <= a.B) return a.ro.off[0];
-  uint32_t t = a.B > 1 ? __umulhi((uint32_t)bag, a.b_magic) : (uint32_t)bag;
-  if (a.B > 1 && (t + 1u) * (uint32_t)a.B <= (uint32_t)bag) ++t;
-  return a.ro.off[t];
+  return a.ro.off[table_of_bag((uint32_t)bag, a.B, a.b_magic)];
 }
 
 __global__ __launch_bounds__(kWave) void k_route_count(RouteArgs a) {
@@ -252,7 +249,7 @@ hipError_t launch_route(const RouteLaunch& p, hipStream_t s) {
   a.N = (int32_t)p.N;
   a.owner_bits = 0;
   while ((1 << a.owner_bits) < p.W) ++a.owner_bits;
-  a.b_magic = p.B > 1 ? (uint32_t)(((uint64_t)1 << 32) / (uint32_t)p.B) : 0u;
+  a.b_magic = bag_magic(p.B);
   a.bags_per_block = plan.bags_per_block;
   a.nblocks = plan.nblocks;
   a.counts = static_cast<int32_t*>(p.ws);
