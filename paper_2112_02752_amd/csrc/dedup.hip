@@ -888,17 +888,22 @@ struct ColScanArgs {
   int32_t tiles, nd, stride;
 };
 
-// One block per kColDigits digits; thread (digit, chunk of consecutive
-// tiles): the chunk's counts are loaded kColBatch at a time, the chunk sums
-// scanned across the block, and the chunk rewritten with running prefixes (from
-// registers where it is one batch: up to 2048 tiles, 8M keys).  Bound by the
-// latency of its loads and the blocks at work: with 16 digits a block, two
-// loads of every count and the sums added one by one it took 11 us for 1340
-// tiles of 256 to 512 digits (16 to 32 blocks).
-constexpr int kColDigits = 8;
-constexpr int kColChunks = 128;
+// One block per DIGITS digits; thread (digit, chunk of consecutive tiles): the
+// chunk's counts are loaded kColBatch at a time, the chunk sums scanned across the
+// block, and the chunk rewritten with running prefixes (from registers where it
+// is one batch).  Bound by the latency of its loads and the blocks at work, and
+// beside other kernels by its traffic: a digit's counts of consecutive tiles lie
+// rows apart, so that a block uses 4 DIGITS bytes of each 128-byte line.  16
+// digits a block: chunks of one batch up to 1024 tiles, where 8 take twice the
+// bytes (50M-row workload, groups of 8, 960 tiles: 10.7 us in the pipelined
+// schedule, 7.2 with 16; 818 tiles alone: 6.4 and 5.4); beyond, 8 (1340 tiles: 7.8
+// us, with 16 9.2).
+constexpr int kColThreads = 1024;
 constexpr int kColBatch = 16;
-__global__ __launch_bounds__(kColDigits * kColChunks) void k_column_scan(ColScanArgs a) {
+constexpr int col_digits(int tiles) { return tiles <= kColThreads / 16 * kColBatch ? 16 : 8; }
+template <int DIGITS>
+__global__ __launch_bounds__(kColThreads) void k_column_scan(ColScanArgs a) {
+  constexpr int kColDigits = DIGITS, kColChunks = kColThreads / DIGITS;
   constexpr int NWd = kColChunks / kWave;  // wavefronts that scan one digit's chunk sums
   __shared__ uint32_t s_cs[kColDigits][kColChunks + 1];
   __shared__ uint32_t s_w[kColDigits * NWd];
@@ -949,6 +954,13 @@ __global__ __launch_bounds__(kColDigits * kColChunks) void k_column_scan(ColScan
 }
 
 // ----------------------------------------------------------------- unique
+
+inline void launch_column_scan(const ColScanArgs& a, hipStream_t s) {
+  if (col_digits(a.tiles) == 16)
+    hipLaunchKernelGGL(k_column_scan<16>, dim3((unsigned)((a.nd + 15) / 16)), dim3(kColThreads), 0, s, a);
+  else
+    hipLaunchKernelGGL(k_column_scan<8>, dim3((unsigned)((a.nd + 7) / 8)), dim3(kColThreads), 0, s, a);
+}
 
 struct UniqArgs {
   const uint32_t* skeys;
@@ -1461,8 +1473,7 @@ hipError_t launch_dedup(const DedupLaunch& p, hipStream_t s) {
       sa.tiles = sort_tiles;
       sa.nd = 1 << xa.bits;
       sa.stride = status_stride;
-      hipLaunchKernelGGL(k_column_scan, dim3((unsigned)((sa.nd + kColDigits - 1) / kColDigits)),
-                         dim3(kColDigits * kColChunks), 0, s, sa);
+      launch_column_scan(sa, s);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       xa.prefix = counts;
     }
@@ -1769,8 +1780,7 @@ hipError_t launch_dedup_group(const GroupDedupLaunch& p, hipStream_t s) {
       sa.tiles = sort_tiles;
       sa.nd = 1 << xa.bits;
       sa.stride = status_stride;
-      hipLaunchKernelGGL(k_column_scan, dim3((unsigned)((sa.nd + kColDigits - 1) / kColDigits)),
-                         dim3(kColDigits * kColChunks), 0, s, sa);
+      launch_column_scan(sa, s);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       xa.prefix = counts;
       e = it == kSortItemsCore ? launch_pass_bits<kSortItemsCore, false>(xa, sort_tiles, s)

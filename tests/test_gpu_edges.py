@@ -257,7 +257,9 @@ _EDGES = [1, 64, 2047, 2048, 2049, 4097, 10_239, 10_240, 10_241, 32_767, 32_768,
 
 # (and so many bags, none empty, that the samples around a tile are sampled again)
 @pytest.mark.parametrize("layout,n", [(x, n) for x in sorted(_LAYOUTS) for n in _EDGES] +
-                         [("one id a bag", 8_400_001), ("one table", 8_400_001)])
+                         [("one id a bag", 8_400_001), ("one table", 8_400_001),
+                          # 1024 and 1025 tiles: the column scan's two forms
+                          ("empty tables", 4_194_304), ("empty tables", 4_194_305)])
 def test_general_dedup_at_its_edges(layout, n):
     """The dedup by sort passes, co-resident and wait-free: every integer output
     exact, the bags through gradient rows that are sums of integers."""
