@@ -3,18 +3,21 @@
 // are those of the general dedup (dedup.hip), bit for bit.
 //
 // What bounds it: one compute unit's vector instructions (a ballot per digit
-// bit and 64 keys), so it is the faster form only up to kSmallKeys keys.  The
+// bit and 64 slots), so it is the faster form only for a few thousand keys.  The
 // general passes spread such a batch over a few workgroups that meet through
 // memory: a kernel boundary of about 3 us and two or three exchanges of 1.5 to
-// 2.5 us a pass, 20 to 37 us for anything up to 60k keys.  Measured (us, general ->
-// here; ids of a 17-bit and of a 26-bit table):
-//    190 keys   20.6 -> 8.7   28.3 -> 8.8
-//   1900        23.6 -> 8.0   32.6 -> 9.9
-//   3900        25.5 -> 11.4  35.4 -> 14.6
-//   5800        25.6 -> 16.0  35.9 -> 20.8
-//   7600        25.7 -> 17.8  35.8 -> 23.6
-// (growing by 2 to 2.5 us per 1000 keys, it would pass the general form's time
-// at about 12000; more than 8192 also leaves no LDS for the bags)
+// 2.5 us a pass, 20 to 37 us for anything up to 60k keys.  A batch pays for the
+// slots of its instance (2, 4 or 8 keys a thread).  Measured (us, general -> here;
+// ids of a 17-bit and of a 26-bit table):
+//    190 keys   20.6 -> 9.1   28.3 -> 9.1
+//   1900        23.6 -> 9.2   32.6 -> 10.3
+//   3900        25.5 -> 11.5  35.4 -> 14.9
+//   4200                15.5          20.0
+//   5800        25.6 -> 16.2  35.9 -> 21.2
+//   7600        25.7 -> 18.0  35.8 -> 23.8
+//   8190                18.5          24.2
+// 8 keys a thread take 117 KB of the 160 KB of LDS; larger batches (12 keys, 157
+// KB) were not tried.
 #include "emb_common.h"
 #include "kernels.h"
 

@@ -910,20 +910,22 @@ __global__ __launch_bounds__(256) void k_update_wave(UArgs a) {
 // Chunks of a batch up to which four, and two, wavefronts share each.  One
 // wavefront to a chunk fills the device once with 7000 to 8000 chunks (7 or 8 to
 // a SIMD), and a few chunks more are a second round of few wavefronts; the parts
-// of a chunk cost its bounds again.  Main kernel and combine, row-wise Adagrad,
-// one / two / four wavefronts to a chunk (us):
-//   64 fp32 values     Zipf 1.2               Zipf 1.05              uniform ids
-//     2.8k chunks      26.1 / 23.6 / 21.0     28.8 / 26.9 / 25.0     28.6 / 28.3 / 27.9
-//     4.8k             29.3 / 25.9 / 26.4     35.6 / 31.0 / 32.0     46.3 / 45.0 / 43.5
-//     8.6k             35.5 / 32.3 / 34.2     46.3 / 42.5 / 43.6     85.6 / 82.2 / 81.9
-//    15.3k             48.5 / 45.1 / 49.9     68.8 / 65.0 / 65.6    136.0 / 133.5 / 135.7
-//    19k               52.4 / 50.2 / -        68.4 / 66.0 / -       125.4 / 121.7 / -
-//    38k               88.5 / 88.5 / -       116.3 / 113.8 / -      202.6 / 206.3 / -
-//   512 bf16 values
-//     5.7k            111.3 / 106.3 / 99.8   141.7 / 133.9 / 128.2  206.4 / 203.7 / 199.5
-//     9.6k            175.2 / 164.8 / 158.6  221.3 / 213.7 / 205.9  331.5 / 322.1 / 319.0
+// of a chunk cost its bounds again.  Gradient rows alone take fewer instructions
+// and registers, and gain less (they are summed by the same parts, so that they
+// are those of the fused step).  Main kernel and combine, six batches in turn, one
+// / two / four wavefronts to a chunk (us):
+//   64 fp32 values       row-wise Adagrad,      the same,              gradient rows alone,
+//                        Zipf 1.2               Zipf 0.9               8 tables, Zipf 1.1
+//     3.7k chunks        28.6 / 25.8 / 24.8     42.8 / 42.8 / 42.5     22.9 / 21.8 / 21.9
+//     5.7k               33.5 / 28.7 / 30.3     54.8 / 51.9 / 54.5     25.6 / 24.6 / 25.4
+//     9.5k               39.3 / 36.2 / 39.1     76.9 / 71.9 / 78.9     31.7 / 31.2 / 33.7
+//    13.4k               47.8 / 45.0 / 50.6     93.5 / 90.9 / 102      39.6 / 41.4 / 46.1
+//    17.2k               57.3 / 55.5 / 64.2      113 / 110 / 125       48.3 / 50.4 / 57.1
+//   256 fp32 values      row-wise Adagrad, Zipf 1.1
+//     3.7k / 9.5k        61.9 / 56.4 / 54.3      124 / 115 / 112
+//    17.2k                200 / 194 / 192
 constexpr int split_four(int el) { return el == 1 ? 5000 : 8192; }
-constexpr int kSplitTwo = 20480;
+constexpr int split_two(int el) { return el == 1 ? 16384 : 20480; }
 
 template <typename TW, int EL, int OPT>
 hipError_t launch_reduce_t(const RArgs& ra, hipStream_t s) {
@@ -984,7 +986,8 @@ hipError_t launch_update_dt(const UArgs& ua, hipStream_t s) {
 
 hipError_t launch_reduce_wave(const RArgs& args, int dtype, hipStream_t s) {
   RArgs ra = args;
-  ra.split = ra.nchunks <= split_four(ra.D <= 64 ? 1 : 2) ? 2 : (ra.nchunks <= kSplitTwo ? 1 : 0);
+  const int el = ra.D <= 64 ? 1 : 2;
+  ra.split = ra.nchunks <= split_four(el) ? 2 : (ra.nchunks <= split_two(el) ? 1 : 0);
   return dtype == EMB_FP32 ? launch_reduce_dt<float>(ra, s) : launch_reduce_dt<uint16_t>(ra, s);
 }
 

@@ -168,7 +168,7 @@ def test_reduce_segment_lengths(dtype, D, name):
 
 
 @pytest.mark.parametrize("dtype,D", [("fp32", 36), ("bf16", 72), ("fp32", 132)])
-@pytest.mark.parametrize("chunks", [5000, 5001, 8192, 8193, 20480, 20481])
+@pytest.mark.parametrize("chunks", [5000, 5001, 8192, 8193, 16384, 16385, 20480, 20481])
 def test_reduce_split_of_chunks(dtype, D, chunks):
     """Batches on both sides of the sizes where four, two and one wavefronts
     share a chunk, segments of all lengths around a chunk's and its parts'; the
@@ -187,7 +187,7 @@ def test_reduce_split_of_chunks(dtype, D, chunks):
 
 
 @pytest.mark.parametrize("D", [36, 48, 64])
-@pytest.mark.parametrize("n", [2048 * 64, 2048 * 64 + 1, 5000 * 64 + 1, 10240 * 64 + 1, 20480 * 64 + 1])
+@pytest.mark.parametrize("n", [2048 * 64, 2048 * 64 + 1, 5000 * 64 + 1, 10240 * 64 + 1, 16384 * 64 + 1])
 def test_unfused_equals_fused_in_both_forms(D, n):
     """Batches on both sides of the sizes where chunks are shared by four, two
     and one wavefronts: a row's sum of squares is formed in one order, whichever
