@@ -729,16 +729,20 @@ __device__ __forceinline__ void level2_sum(const RArgs& a, int g0, int g1, WsHea
     uint32_t spins = 0;
     const uint64_t t0 = wait_clock();
     // the rows of a round are loaded together until all carry their tags
-    // (rows past the last stand in with the first)
+    // (rows past the last stand in with it)
+    const uint64_t* src = a.level2 + (size_t)r0 * 2 * a.D;
 #pragma unroll 1
     for (;;) {
       uint32_t tags = kLevel2Tag;
+      uint32_t off = 0;
 #pragma unroll
       for (int q = 0; q < RR; ++q) {
-        const int r = r0 + q < g1 ? r0 + q : g0;
-        const uint64_t* src = a.level2 + ((size_t)r * 2 + (r == g0 ? 1 : 0)) * a.D;
+        // (the segment's first range left its row in slot 1)
+        const uint64_t* row = src + off + (q == 0 && r0 == g0 ? a.D : 0);
 #pragma unroll
-        for (int v = 0; v < EL; ++v) x[q][v] = ld_relaxed_u64(src + cl.at[v / VW] + v % VW);
+        for (int v = 0; v < EL; ++v) x[q][v] = ld_relaxed_u64(row + cl.at[v / VW] + v % VW);
+        off += r0 + q + 1 < g1 ? 2u * (uint32_t)a.D : 0u;
+        asm("" : "+v"(off));
       }
 #pragma unroll
       for (int q = 0; q < RR; ++q)
@@ -810,24 +814,37 @@ __global__ __launch_bounds__(kCombineThreads) void k_combine_wave(RArgs a) {
       const uint64_t stride = (uint64_t)D * 8u, rows = addr_of(a.partials);
       const float x0 = load_at<float>(rows + (uint64_t)cf * stride + (uint64_t)D * 4u, cl.at[0] * 4u);
       const float x1 = load_at<float>(rows + (uint64_t)cl1 * stride, cl.at[0] * 4u);
-      // (rounds of 32 rows, whole ranges' in two; what is left, and short pieces, in rounds of 8)
-      int i0 = w0;
+      // (rounds of 32 rows, whole ranges' in two; what is left, and short pieces, in
+      // rounds of 8.  Addresses are the piece's first row and a 32-bit offset: a
+      // 64-bit scalar for each of a round's rows is more than there are.)
+      const uint64_t first = rows + (uint64_t)w0 * stride;
+      const uint32_t step = (uint32_t)D * 8u;
+      const int nw = w1 - w0;
+      uint32_t off = cl.at[0] * 8u;
+      int i0 = 0;
 #pragma unroll 1
-      for (; i0 + CU <= w1; i0 += CU) {
+      for (; i0 + CU <= nw; i0 += CU) {
         double x[CU];
 #pragma unroll
-        for (int q = 0; q < CU; ++q) x[q] = load_at<double>(rows + (uint64_t)(i0 + q) * stride, cl.at[0] * 8u);
+        for (int q = 0; q < CU; ++q) {
+          x[q] = load_at<double>(first, off);
+          off += step;
+          asm("" : "+v"(off));  // (not 32 multiples of the step in scalars)
+        }
 #pragma unroll
         for (int q = 0; q < CU; ++q) sum[0] += x[q];
       }
 #pragma unroll 1
-      for (; i0 < w1; i0 += 8) {
+      for (; i0 < nw; i0 += 8) {
         double x[8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q)
-          x[q] = load_at<double>(rows + (uint64_t)min(i0 + q, w1 - 1) * stride, cl.at[0] * 8u);
+        for (int q = 0; q < 8; ++q) {
+          x[q] = load_at<double>(first, off);
+          off += i0 + q + 1 < nw ? step : 0u;
+          asm("" : "+v"(off));
+        }
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sum[0] += i0 + q < w1 ? x[q] : 0.;
+        for (int q = 0; q < 8; ++q) sum[0] += i0 + q < nw ? x[q] : 0.;
       }
       sum[0] += (part0 ? (double)x0 : 0.) + (part1 ? (double)x1 : 0.);
     } else {
