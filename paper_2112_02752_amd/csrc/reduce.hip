@@ -670,17 +670,17 @@ hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
 // 64 fp32 values, row-wise Adagrad, one table of 20M rows, bags of 30 (main
 // kernel and combine, lane groups -> wave form, us; ids uniform / Zipf 0.9 /
 // 1.05 / 1.2):
-//    30k lookups   15.2 -> 13.2   19.6 -> 13.8   18.6 -> 15.7   16.0 -> 15.8
-//   120k           25.8 -> 20.9   29.4 -> 23.9   23.5 -> 21.5   16.5 -> 19.0
-//   305k           49.4 -> 43.8   46.0 -> 38.5   33.1 -> 33.4   23.1 -> 26.8
-//   430k           66.3 -> 61.6   54.9 -> 49.7   39.9 -> 37.1   27.5 -> 29.3
-//   490k           79.8 -> 71.7   59.3 -> 53.6   43.6 -> 40.7   30.1 -> 31.8
-//   730k          130   -> 109    85.1 -> 73.8   57.7 -> 54.0   38.3 -> 38.9
-//   1.2M          212   -> 185   149   -> 122    88.4 -> 79.0   56.3 -> 54.9
-//   3.1M          481   -> 386   342   -> 247   209   -> 175   119   -> 124
+//    30k lookups   15.3 -> 11.5   19.5 -> 13.1   18.6 -> 14.5   16.5 -> 14.7
+//   120k           25.8 -> 21.1   29.7 -> 23.0   22.8 -> 19.9   16.5 -> 17.7
+//   240k           45.0 -> 35.1   39.2 -> 32.8   28.8 -> 27.8   20.2 -> 22.8
+//   305k           49.4 -> 43.4   45.6 -> 36.8   32.8 -> 31.4   23.0 -> 25.6
+//   490k           79.2 -> 71.7   59.6 -> 53.9   43.6 -> 39.3   30.3 -> 29.9
+//   730k          129   -> 108    85.7 -> 73.5   57.6 -> 51.7   37.9 -> 36.8
+//   1.2M          212   -> 188   149   -> 122    88.9 -> 80.7   56.5 -> 55.5
+//   3.1M          482   -> 388   343   -> 245   209   -> 173   119   -> 117
 // The wave form wins by its loads in flight; where most rows of G are in the L2s
 // (the most skewed ids) its instructions per row, and its long segments' sums in
-// double, cost as much, and 2 to 4 us more at 100k to 500k lookups.  Size does not
+// double, cost as much, and 1 to 3 us more at 100k to 370k lookups.  Size does not
 // tell these apart, and how skewed a batch is, the host does not know.
 int clamp_blocks(int64_t want, int lo, int hi) {
   if (want < lo) return lo;

@@ -685,7 +685,7 @@ __global__ __launch_bounds__(256) void k_reduce_wave(RArgs a) {
 // few microseconds of dependent loads, and what it unrolls has to be fetched
 // as instructions first; rows of 128 values: 64 a round took 16 us where 16 take
 // less than 10, with 33 KB of code instead of 8.  Rows of up to 64 values, 50M-row
-// workload: 16 a round 9.4 us, 32 8.7.)
+// workload: 16 a round 9.4 us, 32 8.7, and 7.5 with addresses of less code.)
 constexpr int combine_rows(int el) { return el == 1 ? 32 : (el == 2 ? 16 : (el == 4 ? 8 : (el == 8 ? 4 : 2))); }
 constexpr int level2_rows(int el) { return combine_rows(el) / 2; }
 
