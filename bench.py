@@ -618,8 +618,8 @@ def main():
     phases = {}
     for name, kern in (("fwd", "k_pool_fwd (emb_pool_fwd)"),
                        ("dedup", dedup_kernels),
-                       ("bwd_update", "k_reduce_main + k_reduce_combine, or k_reduce_wave + k_combine_wave by row width and "
-                        "batch size (emb_grad_reduce, fused update)")):
+                       ("bwd_update", "k_reduce_main + k_reduce_combine (rows of at most 32 values), or k_reduce_wave + "
+                        "k_combine_wave (emb_grad_reduce, fused update)")):
         log_b, comp_b = models[name]
         t = t_phase[name]
         phases[name] = {"kernels": kern, "avg_us": t * 1e6, "logical_bytes": log_b, "compulsory_bytes": comp_b,
