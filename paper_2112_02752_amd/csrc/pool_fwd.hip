@@ -27,10 +27,10 @@
 // enough.  Merging repeats by hash classes, LDS shuffles and a select per
 // element, the kernel issued 640 vector instructions per bag of the 26-table
 // bf16 workload (136M per call, about the kernel's whole 200 us on 1024 SIMDs
-// at 4 cycles each); it issues 45M now and takes 135 us at 5.0 TB/s of L2 miss
-// traffic (571 MB read, 109 MB written), the rate of a large device copy.  One
+// at 4 cycles each); it issues 46M now and takes 134 us at 5.0 TB/s of L2 miss
+// traffic (572 MB read, 109 MB written), the rate of a large device copy.  One
 // 50M-row table, 16384 bags of 30 ids: 14-15 us either way (latency of four
-// dependent loads); 8 tables of 1M rows: 22 -> 18.5 us (4.8 TB/s).
+// dependent loads); 8 tables of 1M rows: 22 -> 17 us (5.3 TB/s).
 //
 // Short bags: a wavefront per bag of one id leaves 63/64 of its loads unused
 // and takes as long as a full one, so when the bags of a wavefront and its

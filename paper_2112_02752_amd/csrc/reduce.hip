@@ -682,6 +682,7 @@ hipError_t launch_update_dt(const UArgs& ua, int blocks, hipStream_t s) {
 // (the most skewed ids) its instructions per row, and its long segments' sums in
 // double, cost as much, and 1 to 3 us more at 100k to 370k lookups.  Size does not
 // tell these apart, and how skewed a batch is, the host does not know.
+
 int clamp_blocks(int64_t want, int lo, int hi) {
   if (want < lo) return lo;
   if (want > hi) return hi;

@@ -20,15 +20,15 @@
 //
 // What bounds it: the L2s' misses (gradient rows, and table rows read and
 // written).  200M-row-like long tail (64 fp32 values, 3.3M lookups, SGD): 337
-// -> 231 us, 1.6 GB of L2 misses at 6.9 TB/s; there lane groups (reduce.hip)
+// -> 234 us, 1.6 GB of L2 misses at 6.9 TB/s; there lane groups (reduce.hip)
 // wait for the longest of a wavefront's 16 segments and load stand-in rows for
 // the rest.  26 tables of 128 bf16 values, 5.5M lookups, row-wise Adagrad: 510
-// -> 318 us: neighbouring chunks run at the same time on all of the chip, so
+// -> 321 us: neighbouring chunks run at the same time on all of the chip, so
 // one table's gradient rows (4 MB) are used while they are in the L2s (2.53 ->
-// 1.28 GB read); with light and heavy segments on wavefronts of their own,
+// 1.27 GB read); with light and heavy segments on wavefronts of their own,
 // several tables' rows were live at once.  It is then bound by instruction
-// issue (1500 vector and 900 scalar a chunk) as much as by misses (4.9 TB/s).
-// Element-wise Adagrad, 104 bf16 values, 277k lookups: 99 -> 67 us (stochastic
+// issue (1350 vector and 750 scalar a chunk) as much as by misses (4.8 TB/s).
+// Element-wise Adagrad, 104 bf16 values, 277k lookups: 99 -> 65 us (stochastic
 // rounding's 64-bit products are half of its instructions).
 // Measured and not kept: chunks dealt to the XCDs in runs of 16 to 4096
 // (nothing gained, the largest lose), the next batch's rows loaded during the
